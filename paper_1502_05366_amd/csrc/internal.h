@@ -46,28 +46,26 @@ hipError_t launch_narrow(bool f32, bool trans, const void* A, int64_t lda, const
                          int64_t ldx, void* C, int64_t ldc, int64_t M, int64_t K, int64_t L,
                          int ncu, void* work, size_t work_bytes, hipStream_t s);
 
-// BF16 passes: C (FP32) = op(A) X with A in BF16 (lda % 8 == 0, 16-byte
-// aligned) and Xt = X^T in BF16 (L x ldx, ldx = rup(K, 8)); L <= 256.
-GemmPlan plan_gemm_bf16(int64_t M, int64_t K, int64_t L, int ncu);
-size_t gemm_bf16_part_bytes(const GemmPlan& p);
+// BF16 passes: C (FP32) = op(A) X, or C += op(A) X with accumulate, with A in
+// BF16 (lda % 8 == 0, 16-byte aligned) and Xt = X^T in BF16 (rup(L, 16) rows, L
+// of them used, ldx % 8 == 0, zero from K to ldx).  part: gemm_bf16_part_bytes
+// bytes for any number of compute units up to the one asked for (with less,
+// the reduction is not split).
+size_t gemm_bf16_part_bytes(int64_t M, int64_t K, int64_t L, int ncu);
 hipError_t launch_gemm_bf16(bool trans, const uint16_t* A, int64_t lda, const uint16_t* Xt,
                             int64_t ldx, float* C, int64_t ldc, int64_t M, int64_t K, int64_t L,
-                            const GemmPlan& p, void* part, size_t part_cap, hipStream_t s);
-// the same, adding to C
-hipError_t launch_gemm_bf16_acc(bool trans, const uint16_t* A, int64_t lda, const uint16_t* Xt,
-                                int64_t ldx, float* C, int64_t ldc, int64_t M, int64_t K,
-                                int64_t L, const GemmPlan& p, void* part, size_t part_cap,
-                                hipStream_t s);
+                            int ncu, void* part, size_t part_cap, bool accumulate,
+                            hipStream_t s);
 // FP8 passes: C (FP32) = op(A8) X' with A8 FP8 E4M3 codes (lda % 16 == 0,
-// 16-byte aligned) and Xt the E4M3 codes of X' transposed (L x ldx, ldx =
-// rup(K, 16)), scaled in the epilogue by the column scales of X' (xscale, L)
-// and, for the transposed pass, by row scales (rscale, M; may be null).
-GemmPlan plan_gemm_f8(int64_t M, int64_t K, int64_t L, int ncu);
-size_t gemm_f8_part_bytes(const GemmPlan& p);
+// 16-byte aligned) and Xt the E4M3 codes of X' transposed (rup(L, 16) rows,
+// ldx % 16 == 0, zero from K to ldx), scaled by the column scales of X'
+// (xscale, L) and, for the transposed pass, by row scales (rscale, M; may be
+// null).  part as above.
+size_t gemm_f8_part_bytes(int64_t M, int64_t K, int64_t L, int ncu);
 hipError_t launch_gemm_f8(bool trans, const uint8_t* A, int64_t lda, const uint8_t* Xt,
                           int64_t ldx, const float* xscale, const float* rscale, float* C,
-                          int64_t ldc, int64_t M, int64_t K, int64_t L, const GemmPlan& p,
-                          void* part, size_t part_cap, bool accumulate, hipStream_t s);
+                          int64_t ldc, int64_t M, int64_t K, int64_t L, int ncu, void* part,
+                          size_t part_cap, bool accumulate, hipStream_t s);
 // Xt[c][k] = e4m3(X'(k, c) / t[c]), t[c] = max_k |X'(k, c)| / 448, with X'(k, c)
 // = rowscale[k] X(k, c) (rowscale may be null), or with prev (the codes of a
 // first term, ld ldp, scales t0) the residual X'(k, c) - t0[c] dec(prev[c][k]).

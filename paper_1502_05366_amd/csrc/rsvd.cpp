@@ -199,12 +199,12 @@ size_t max_part(const Shape& s) {
     b = std::max(b, narrow_work_bytes(s.f32, true, s.n, s.m, s.l, ncu));
   }
   if (s.bf16) {
-    b = std::max(b, gemm_bf16_part_bytes(plan_gemm_bf16(s.m, s.n, s.l, ncu)));
-    b = std::max(b, gemm_bf16_part_bytes(plan_gemm_bf16(s.n, s.m, s.l, ncu)));
+    b = std::max(b, gemm_bf16_part_bytes(s.m, s.n, s.l, ncu));
+    b = std::max(b, gemm_bf16_part_bytes(s.n, s.m, s.l, ncu));
   }
   if (s.f8) {
-    b = std::max(b, gemm_f8_part_bytes(plan_gemm_f8(s.m, s.n, s.l, ncu)));
-    b = std::max(b, gemm_f8_part_bytes(plan_gemm_f8(s.n, s.m, s.l, ncu)));
+    b = std::max(b, gemm_f8_part_bytes(s.m, s.n, s.l, ncu));
+    b = std::max(b, gemm_f8_part_bytes(s.n, s.m, s.l, ncu));
   }
   upd(s.m, s.l, s.k);
   upd(s.n, s.l, s.k);
@@ -429,7 +429,7 @@ hipError_t pass(Ctx& c, int atype, bool trans, int64_t m, int64_t n, int l, cons
     // quantized per column; with split a second term holds its residual
     const int64_t ldt = rup(K, 16);
     const int lp = (int)rup(l, 16);
-    const GemmPlan pg = plan_gemm_f8(M, K, l, std::min(c.ncu, NCU_CAP));
+    const int ncu = std::min(c.ncu, NCU_CAP);
     const float* xs = trans ? nullptr : c.f8.ascale;     // folded into X' for Y = A X
     const float* rs = trans ? c.f8.ascale : nullptr;     // epilogue row scale for A^T X
     uint8_t* x0 = c.f8.xt;
@@ -437,13 +437,13 @@ hipError_t pass(Ctx& c, int atype, bool trans, int64_t m, int64_t n, int l, cons
     RSVD_TRY(launch_quant_x_f8(true, X, ldx, K, l, xs, nullptr, 0, nullptr, x0, ldt, c.f8.t,
                                c.f8.tmax, c.st));
     RSVD_TRY(launch_gemm_f8(trans, static_cast<const uint8_t*>(A), lda, x0, ldt, c.f8.t, rs,
-                            static_cast<float*>(Y), ldy, M, K, l, pg, part, part_bytes, false,
+                            static_cast<float*>(Y), ldy, M, K, l, ncu, part, part_bytes, false,
                             c.st));
     if (!split) return hipSuccess;
     RSVD_TRY(launch_quant_x_f8(true, X, ldx, K, l, xs, x0, ldt, c.f8.t, x1, ldt, c.f8.t + lp,
                                c.f8.tmax, c.st));
     return launch_gemm_f8(trans, static_cast<const uint8_t*>(A), lda, x1, ldt, c.f8.t + lp, rs,
-                          static_cast<float*>(Y), ldy, M, K, l, pg, part, part_bytes, true, c.st);
+                          static_cast<float*>(Y), ldy, M, K, l, ncu, part, part_bytes, true, c.st);
   }
   if (atype < 2 && narrow_applies(atype == 1, lda, A, l) &&
       narrow_work_bytes(atype == 1, trans, M, K, l, std::min(c.ncu, NCU_CAP)) <= part_bytes)
@@ -454,16 +454,18 @@ hipError_t pass(Ctx& c, int atype, bool trans, int64_t m, int64_t n, int l, cons
     return launch_gemm(atype == 1 ? GEMM_FFFF : GEMM_DDDD, trans, A, lda, X, ldx, Y, ldy, M, K, l,
                        pg, part, part_bytes, c.st);
   }
-  const int64_t ldt = rup(K, 32);   // (the BF16 passes read whole 32-deep k-steps of Xt)
-  const GemmPlan pg = plan_gemm_bf16(M, K, l, std::min(c.ncu, NCU_CAP));
+  const int64_t ldt = rup(K, 32);
+  const int ncu = std::min(c.ncu, NCU_CAP);
   RSVD_TRY(launch_convert_bf16(true, X, ldx, K, l, xt, ldt, c.st));
   RSVD_TRY(launch_gemm_bf16(trans, static_cast<const uint16_t*>(A), lda, xt, ldt,
-                            static_cast<float*>(Y), ldy, M, K, l, pg, part, part_bytes, c.st));
+                            static_cast<float*>(Y), ldy, M, K, l, ncu, part, part_bytes, false,
+                            c.st));
   if (!split) return hipSuccess;
   // X_lo = X - bf16(X), then Y += A X_lo
   RSVD_TRY(launch_bf16_residual(static_cast<const float*>(X), ldx, K, l, xt, ldt, c.st));
-  return launch_gemm_bf16_acc(trans, static_cast<const uint16_t*>(A), lda, xt, ldt,
-                              static_cast<float*>(Y), ldy, M, K, l, pg, part, part_bytes, c.st);
+  return launch_gemm_bf16(trans, static_cast<const uint16_t*>(A), lda, xt, ldt,
+                          static_cast<float*>(Y), ldy, M, K, l, ncu, part, part_bytes, true,
+                          c.st);
 }
 
 struct Outs {
@@ -1548,7 +1550,7 @@ size_t rsvd_pass_workspace_bytes(int dtype, int trans, int64_t m, int64_t n, int
   const int64_t M = trans ? n : m, K = trans ? m : n;
   if (dtype == RSVD_BF16) {
     if (l > MAX_L_SVD) return 0;
-    return gemm_bf16_part_bytes(plan_gemm_bf16(M, K, l, NCU_CAP)) + 256 +
+    return gemm_bf16_part_bytes(M, K, l, NCU_CAP) + 256 +
            (size_t)rup(l, 16) * rup(K, 32) * sizeof(uint16_t) + 256;
   }
   return std::max(gemm_part_bytes(plan_gemm(M, K, l, NCU_CAP, 0), 8),
@@ -1559,7 +1561,7 @@ size_t f8_pass_layout(int trans, int64_t m, int64_t n, int64_t l, void* base, F8
                       void** part, size_t* part_bytes) {
   const int64_t M = trans ? n : m, K = trans ? m : n;
   const int lp = (int)rup(l, 16);
-  const size_t pb = gemm_f8_part_bytes(plan_gemm_f8(M, K, l, NCU_CAP));
+  const size_t pb = gemm_f8_part_bytes(M, K, l, NCU_CAP);
   Arena a(base);
   F8Bufs b;
   b.xt = a.take<uint8_t>((size_t)2 * lp * rup(K, 16));
