@@ -61,7 +61,8 @@ struct Args {
   float* C; int64_t ldc;
   int64_t M, K, L;                 // elements
   int64_t nrt, nct;
-  int S;                           // k splits (S > 1: partial tiles in part)
+  int64_t P, W;                    // tile numbers; the first W are whole tiles,
+  int S;                           // the others in S k splits (partial tiles in part)
   float* part;
   const float* xs;                 // FP8: L column scales (null: none)
   const float* rs;                 // FP8: M row scales (null: none)
@@ -200,24 +201,28 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
   const int c = lane & 15;
   const int q = lane >> 4;
 
-  // workgroup -> (row tile, column tile, split).  Workgroups are dealt to the
-  // XCDs in turn (w % 8).  Those of one XCD that run at the same time take
-  // the column tiles of one row tile (the second read of A hits that XCD's
-  // L2) and the same k split of different row tiles (the same lines of Xt).
+  // Workgroup -> (tile, split).  Tiles are numbered so that number p runs on
+  // XCD p % 8 (workgroups are dealt to the XCDs in turn) and the workgroups of
+  // one XCD that run at the same time take the column tiles of one row tile
+  // (the second read of A hits that XCD's L2) and the same k range of different
+  // row tiles (the same lines of Xt).  The first g.W tiles are whole, the others
+  // in S splits.  Numbers past the last row tile (of 8) have no tile.
   const int64_t w = blockIdx.x;
-  const int64_t xcd = w % 8, j0 = w / 8;
-  const int64_t rq_n = (g.nrt + 7) / 8;
-  const int64_t ct = j0 % g.nct, jr = j0 / g.nct;
-  const int64_t rt = xcd + 8 * (jr % rq_n);
-  const int sp = (int)(jr / rq_n);
-  if (rt >= g.nrt || sp >= g.S) return;           // (the whole workgroup)
+  const int64_t rest = g.P - g.W;
+  const bool whole = w < g.W;
+  const int64_t p = whole ? w : g.W + (w - g.W) % rest;
+  const int S = whole ? 1 : g.S;
+  const int sp = whole ? 0 : (int)((w - g.W) / rest);
+  const int64_t ct = (p / 8) % g.nct;
+  const int64_t rt = p % 8 + 8 * (p / 8 / g.nct);
+  if (rt >= g.nrt) return;                        // (the whole workgroup)
   const int64_t row0 = rt * BM;
   const int64_t col0 = ct * BN;
   // pairs of whole k-steps are dealt to the splits; what is left (less than
   // two steps) goes to the last split's masked steps
   const int64_t npair = g.K / (2 * KS);
-  const int64_t kb = 2 * ((sp * npair) / g.S);
-  const int64_t ke = 2 * (((sp + 1) * npair) / g.S);
+  const int64_t kb = 2 * ((sp * npair) / S);
+  const int64_t ke = 2 * (((sp + 1) * npair) / S);
 
   // --- addresses -----------------------------------------------------------
   const int64_t m0 = row0 + wave * 64;            // the wave's first row
@@ -237,13 +242,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
   const uint8_t* xp = g.X + (lane >> 3) * g.ldx + 16 * ((lane & 7) ^ (lane >> 3));
   const int64_t xlast = rup(g.L, 16) - 8;
 
+  auto dma1 = [&](int i, int64_t kt, int b) {     // load i of k-step kt into stage b
+    const int64_t gj = min(col0 + (wave + NW * i) * 8, xlast);
+    __builtin_amdgcn_global_load_lds((gbl_vp)(xp + (gj * g.ldx + kt * SB)),
+                                     (lds_vp)(sm + b * STAGE + (wave + NW * i) * 1024), 16, 0, 0);
+  };
   auto dma = [&](int64_t kt, int b) {
 #pragma unroll
-    for (int i = 0; i < NDMA; ++i) {
-      const int64_t gj = min(col0 + (wave + NW * i) * 8, xlast);
-      __builtin_amdgcn_global_load_lds((gbl_vp)(xp + (gj * g.ldx + kt * SB)),
-                                       (lds_vp)(sm + b * STAGE + (wave + NW * i) * 1024), 16, 0, 0);
-    }
+    for (int i = 0; i < NDMA; ++i) dma1(i, kt, b);
   };
   typedef Raw<ELT, TRANS> raw_t;
   typedef typename raw_t::vec avec;
@@ -252,9 +258,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
     if constexpr (!TRANS) return ap[i >> 1] + (k0 * ELT + 64 * (i & 1));
     else return ap[0] + (k0 + (i / (16 / ELT)) * (64 / ELT) + i % (16 / ELT)) * g.lda;
   };
+  auto aload1 = [&](raw_t& r, int i, int64_t kt) {
+    r.v[i] = *reinterpret_cast<const avec*>(aaddr(i, kt * KS));
+  };
   auto aload = [&](raw_t& r, int64_t kt) {
 #pragma unroll
-    for (int i = 0; i < raw_t::N; ++i) r.v[i] = *reinterpret_cast<const avec*>(aaddr(i, kt * KS));
+    for (int i = 0; i < raw_t::N; ++i) aload1(r, i, kt);
   };
 
   f4 acc[4][NB];
@@ -280,28 +289,41 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
   // come after the group's first product: with direct-to-LDS loads in flight
   // the compiler waits for every LDS read there, so these must not be among them.
   // The two products of a BF16 step on one block are 4 GB products apart.
-  auto step = [&](const Opnd<ELT> (&av)[4], const uint8_t* st, const uint8_t* nx, int s0) {
+  // load(i), i < NV, issues the step's memory loads, spread evenly over its
+  // products: issued together they queue at the address unit (16 cycles per
+  // load, four waves), and the wave issues no product meanwhile (2.4 -> 1.9 ms
+  // per pass at 65536 x 32768, l = 576, BF16).
+  constexpr int KPM = ELT == 2 ? 2 : 1;           // products per block and step
+  constexpr int NM = 4 * NB * KPM;
+  constexpr int NV = NA + NDMA;
+  auto step = [&](const Opnd<ELT> (&av)[4], const uint8_t* st, const uint8_t* nx, int s0,
+                  auto&& load) {
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
       const int cur = (s0 + i) & 1;
 #pragma unroll
-      for (int x = 0; x < 4 * GB; ++x) {
-        const int j = x / 4, rb = x % 4;
-        if (i * GB + j < 16) mma<ELT, true, 0>(acc[rb][i * GB + j], av[rb], bq[cur][j]);
-        else mma<ELT, false, 0>(acc[rb][i * GB + j], av[rb], bq[cur][j]);
+      for (int x = 0; x < 4 * GB * KPM; ++x) {
+        const int j = (x / 4) % GB, rb = x % 4;
+        f4& a = acc[rb][i * GB + j];
+        if (x < 4 * GB) {
+          if (i * GB + j < 16) mma<ELT, true, 0>(a, av[rb], bq[cur][j]);
+          else mma<ELT, false, 0>(a, av[rb], bq[cur][j]);
+        } else {
+          if (i * GB + j < 16) mma<ELT, true, KPM - 1>(a, av[rb], bq[cur][j]);
+          else mma<ELT, false, KPM - 1>(a, av[rb], bq[cur][j]);
+        }
         if (x == 0) {
           __builtin_amdgcn_sched_barrier(0);
           if (i + 1 < NG) bread(cur ^ 1, st, i + 1);
           else bread(cur ^ 1, nx, 0);
           __builtin_amdgcn_sched_barrier(0);
         }
-      }
-      if constexpr (ELT == 2) {
+        const int m = i * 4 * GB * KPM + x;       // this product's number
 #pragma unroll
-        for (int x = 0; x < 4 * GB; ++x) {
-          const int j = x / 4, rb = x % 4;
-          if (i * GB + j < 16) mma<ELT, true, 1>(acc[rb][i * GB + j], av[rb], bq[cur][j]);
-          else mma<ELT, false, 1>(acc[rb][i * GB + j], av[rb], bq[cur][j]);
+        for (int v = m * NV / NM; v < (m + 1) * NV / NM; ++v) {
+          __builtin_amdgcn_sched_barrier(0);
+          load(v);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -333,19 +355,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
       for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) av[rb].set(kk, operand<ELT, TRANS>(r, rb, kk));
-      __builtin_amdgcn_sched_barrier(0);
-      aload(r, min(t + 2, last));
-      dma(min(t + 3, last), (int)((t - kb + 3) % NS));
       opnd_settle();
       __builtin_amdgcn_sched_barrier(0);
-      step(av, sm + (int)((t - kb) % NS) * STAGE, sm + (int)((t - kb + 1) % NS) * STAGE, s0);
+      const int64_t ta = min(t + 2, last), tx = min(t + 3, last);
+      const int bx = (int)((t - kb + 3) % NS);
+      step(av, sm + (int)((t - kb) % NS) * STAGE, sm + (int)((t - kb + 1) % NS) * STAGE, s0,
+           [&](int v) {
+             if (v < NA) aload1(r, v, ta);
+             else dma1(v - NA, tx, bx);
+           });
     };
     for (int64_t t = kb; t < ke; t += 2) {        // (each buffer keeps its registers)
       kstep(r0, t, 0);
       kstep(r1, t + 1, NG & 1);
     }
   }
-  if (sp == g.S - 1) {
+  if (sp == S - 1) {
     // the rest: both operands masked to zero past K
     for (int64_t k0 = 2 * npair * KS; k0 < g.K; k0 += KS) {
       wait_vm<0>();
@@ -384,14 +409,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
       __syncthreads();
       opnd_settle();
       bread(0, sm, 0);
-      step(av, sm, sm, 0);
+      step(av, sm, sm, 0, [](int) {});
     }
   }
 
   acc_settle();
   // --- results -------------------------------------------------------------
   // row of element v of block rb: 16 rb + 4 q + v, or 4 (4 q + v) + rb transposed
-  float* P = g.S > 1 ? g.part + ((rt * g.nct + ct) * g.S + sp) * (int64_t)(BM * BN) : nullptr;
+  float* P = S > 1 ? g.part + ((p - g.W) * S + sp) * (int64_t)(BM * BN) : nullptr;
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
@@ -423,9 +448,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
 template <int ELT, int NB>
 __global__ __launch_bounds__(256) void split_sum_kernel(Args g) {
   constexpr int BN = 16 * NB;
-  const int64_t tile = blockIdx.x;
-  const int64_t row0 = (tile / g.nct) * BM;
-  const int64_t col0 = (tile % g.nct) * BN;
+  const int64_t tile = blockIdx.x, p0 = g.W + tile;
+  const int64_t row0 = (p0 % 8 + 8 * (p0 / 8 / g.nct)) * BM;
+  const int64_t col0 = (p0 / 8 % g.nct) * BN;
   const int e = (blockIdx.y * 256 + threadIdx.x) * 4;
   if (e >= BM * BN) return;
   const int64_t r = row0 + e / BN;
@@ -460,45 +485,51 @@ hipError_t run(const Args& g, hipStream_t s) {
   hipError_t e = hipFuncSetAttribute((const void*)pass_kernel<ELT, TRANS, NB>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
   if (e != hipSuccess) return e;
-  const unsigned grid = (unsigned)(8 * g.nct * cdiv(g.nrt, 8) * g.S);
-  hipLaunchKernelGGL((pass_kernel<ELT, TRANS, NB>), dim3(grid), dim3(NT), shm, s, g);
+  const int64_t rest = g.P - g.W;
+  hipLaunchKernelGGL((pass_kernel<ELT, TRANS, NB>), dim3((unsigned)(g.W + rest * g.S)), dim3(NT),
+                     shm, s, g);
   e = hipGetLastError();
   if (e != hipSuccess || g.S == 1) return e;
   hipLaunchKernelGGL((split_sum_kernel<ELT, NB>),
-                     dim3((unsigned)(g.nrt * g.nct), (unsigned)cdiv(BM * 16 * NB, 1024)), dim3(256),
-                     0, s, g);
+                     dim3((unsigned)rest, (unsigned)cdiv(BM * 16 * NB, 1024)), dim3(256), 0, s, g);
   return hipGetLastError();
 }
 
-// The tiling of a pass: column blocks per tile, tiles, splits of the reduction.
+// The tiling of a pass: column blocks per tile, tiles, and how the last round
+// over the compute units (one workgroup each) is filled: the first W tile
+// numbers are whole tiles in full rounds, the `rest` others run in S splits of
+// the reduction, S minimizing the rounds they take times the k-steps of a
+// split, with 8 steps added for a workgroup's start, its partial tile and the
+// sum (258 tiles on 256 compute units: 2 rounds whole, 1 + 1/16 split).  At
+// least 8 steps per split, and at most 2 ncu partial tiles of up to 256 columns.
 struct Plan {
   int nb, S;
-  int64_t nrt, nct;
+  int64_t nrt, nct, P, W;
 };
-// S minimizes the rounds over the compute units (one workgroup each) times the
-// k-steps of a split, with 8 steps added for a workgroup's start, its partial
-// tile and the sum: one tile per workgroup when the tiles fill whole rounds,
-// more splits when they leave a last round mostly idle.  At least 8 steps per
-// split, and at most 2 ncu partial tiles of up to 256 columns of workspace.
 inline Plan plan(int elt, int64_t M, int64_t K, int64_t L, int ncu) {
   Plan p;
   col_tiles(L, p.nct, p.nb);
   p.nrt = cdiv(M, BM);
-  const int64_t T = p.nrt * p.nct, steps = K / (SB / elt);   // (whole k-steps)
+  p.P = 8 * p.nct * cdiv(p.nrt, 8);
+  p.W = ncu % 8 ? p.P : p.P / ncu * ncu;          // (multiples of 8)
+  const int64_t rest = p.P - p.W, steps = K / (SB / elt);   // (whole k-steps)
+  // tile numbers of the rest that have a tile (the padding ends at once)
+  const int64_t pad = p.P - p.nct * p.nrt, live = rest > pad ? rest - pad : rest;
   p.S = 1;
-  double best = (double)cdiv(T, ncu) * (double)steps;
+  double best = (double)cdiv(live, ncu) * (double)steps;
   for (int64_t S = 2; S <= steps / 8; ++S) {
-    if (T * S * 16 * p.nb > (int64_t)2 * ncu * (16 * p.nb < 256 ? 16 * p.nb : 256)) break;
-    const double t = (double)cdiv(T * S, ncu) * ((double)cdiv(steps, S) + 8.0);
+    if (rest * S * 16 * p.nb > (int64_t)2 * ncu * (16 * p.nb < 256 ? 16 * p.nb : 256)) break;
+    const double t = (double)cdiv(live * S, ncu) * ((double)cdiv(steps, S) + 8.0);
     if (t < best) {
       best = t;
       p.S = (int)S;
     }
   }
+  if (p.S == 1) p.W = p.P;
   return p;
 }
 inline size_t part_bytes(const Plan& p) {
-  return p.S > 1 ? (size_t)(p.nrt * p.nct * p.S) * (size_t)(BM * 16 * p.nb) * sizeof(float) : 0;
+  return p.S > 1 ? (size_t)((p.P - p.W) * p.S) * (size_t)(BM * 16 * p.nb) * sizeof(float) : 0;
 }
 
 // Fills in the tiling and launches (whole tiles when `part_cap` bytes do not
@@ -508,7 +539,10 @@ hipError_t launch(Args g, int ncu, size_t part_cap, hipStream_t s) {
   const Plan p = plan(ELT, g.M, g.K, g.L, ncu);
   g.nct = p.nct;
   g.nrt = p.nrt;
-  g.S = part_bytes(p) <= part_cap ? p.S : 1;
+  g.P = p.P;
+  const bool fits = part_bytes(p) <= part_cap;
+  g.S = fits ? p.S : 1;
+  g.W = fits ? p.W : p.P;
   switch (p.nb) {
     case 2: return run<ELT, TRANS, 2>(g, s);
     case 4: return run<ELT, TRANS, 4>(g, s);
