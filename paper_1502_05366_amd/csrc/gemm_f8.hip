@@ -23,135 +23,163 @@ namespace {
 
 // ---- the skinny operand in FP8 ---------------------------------------------
 //
-// E4M3 code of an FP32 value (nearest, ties to even, saturated to +-448; NaN
-// to 0x7F): with e the binary exponent of |y| (at least -6, the smallest
-// normal), the spacing is 2^(e-3); the rounded magnitude is re-read as
-// (exponent, significand) fields.
-__device__ __forceinline__ uint8_t e4m3_from_float(float y) {
-  if (y != y) return 0x7F;
-  const uint32_t sign = y < 0.f ? 0x80u : 0u;
-  const float a = fabsf(y);
-  uint32_t code;
-  if (a >= 448.f) {
-    code = 0x7E;
-  } else {
-    int e;
-    (void)frexpf(a, &e);                       // a = f 2^e, f in [0.5, 1)
-    const int E = max(e - 1, -6);
-    const float step = ldexpf(1.f, E - 3);
-    const float q = fminf(rintf(a / step) * step, 448.f);
-    if (q >= 0x1.0p-6f) {
-      int e2;
-      (void)frexpf(q, &e2);
-      const int E2 = e2 - 1;
-      const uint32_t mant = (uint32_t)rintf((ldexpf(q, -E2) - 1.f) * 8.f);
-      code = ((uint32_t)(E2 + 7) << 3) | mant;
-    } else {
-      code = (uint32_t)rintf(q * 512.f);
-    }
-  }
-  return (uint8_t)(code | sign);
+// E4M3 codes of four FP32 values (nearest, ties to even, saturated to +-448;
+// NaN to 0x7F), packed with the first in the low byte.  The conversion
+// instruction rounds to nearest even down to the subnormals; its input is
+// clamped, since it does not saturate (checked against the definition over
+// every FP32 value: only -0 differs, in its sign).
+__device__ __forceinline__ float e4m3_clamp(float y) {
+  return fminf(fmaxf(y, -448.f), 448.f);           // (NaN is put back below)
+}
+__device__ __forceinline__ uint32_t e4m3_pack(const float (&y)[4]) {
+  int w = __builtin_amdgcn_cvt_pk_fp8_f32(e4m3_clamp(y[0]), e4m3_clamp(y[1]), 0, false);
+  w = __builtin_amdgcn_cvt_pk_fp8_f32(e4m3_clamp(y[2]), e4m3_clamp(y[3]), w, true);
+  uint32_t u = (uint32_t)w;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (y[j] != y[j]) u = (u & ~(0xFFu << (8 * j))) | (0x7Fu << (8 * j));
+  return u;
 }
 
-__device__ __forceinline__ float e4m3_to_float(uint8_t c) {
-  const int e = (c >> 3) & 0xF, m = c & 7;
-  const float v = e == 0 ? (float)m * 0x1.0p-9f : ldexpf(1.f + (float)m * 0.125f, e - 7);
-  return (c & 0x80) ? -v : v;
+// value of code J of a word of four
+template <int J> __device__ __forceinline__ float e4m3_value(uint32_t w) {
+  return __builtin_amdgcn_cvt_f32_fp8((int)w, J);
 }
 
-// Element (k, c) of the operand being quantized: X'(k, c) = s_k X(k, c) (s may
-// be null), or in residual mode the part that the first term leaves,
-// X'(k, c) - t0_c dec(X8_0[c][k]).
-template <typename TX>
-__device__ __forceinline__ float xval(const TX* X, int64_t ldx, const float* s, int64_t k, int c,
-                                      const uint8_t* prev, int64_t ldp, const float* t0) {
-  float v = (float)X[k * ldx + c];
-  if (s) v *= s[k];
-  if (prev) v -= t0[c] * e4m3_to_float(prev[(int64_t)c * ldp + k]);
-  return v;
+// The operand being quantized: X'(k, c) = s_k X(k, c) (s may be null), or for
+// the second term the part that the first leaves, X'(k, c) - t0_c dec(X8_0[c][k]).
+template <int J> __device__ __forceinline__ float residual(float x, float t0, uint32_t codes) {
+  return x - t0 * e4m3_value<J>(codes);
+}
+
+// t = tmax / 448 (1 for a zero column)
+__device__ __forceinline__ float col_scale(uint32_t tmax) {
+  const float m = __uint_as_float(tmax);
+  return m > 0.f ? m / 448.f : 1.f;
 }
 
 // tmax[c] = max_k |X'(k, c)| as FP32 bits (non-negative floats order as
-// integers); tmax zeroed beforehand.  Block: 64 columns x 4 row groups.
+// integers; a maximum does not depend on the order); tmax zeroed beforehand.
+// Block: 64 columns x 4 row groups, eight loads in flight per thread, one
+// atomic per column and workgroup.
 template <typename TX>
 __global__ __launch_bounds__(256) void colmax_kernel(const TX* __restrict__ X, int64_t ldx,
-                                                     int64_t rows, int cols, const float* s,
-                                                     const uint8_t* prev, int64_t ldp,
-                                                     const float* t0, uint32_t* tmax) {
+                                                     int64_t rows, int cols,
+                                                     const float* __restrict__ s,
+                                                     uint32_t* tmax) {
+  constexpr int U = 8;
   __shared__ float part[4][64];
   const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int rg = threadIdx.x >> 6;
-  // four independent maxima (a maximum does not depend on the order), so
-  // that four loads per thread are in flight
-  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
-  if (c < cols) {
-    const int64_t st = (int64_t)gridDim.y * 4;
-    int64_t k = blockIdx.y * 4 + rg;
-    for (; k + 3 * st < rows; k += 4 * st) {
-      m0 = fmaxf(m0, fabsf(xval(X, ldx, s, k, c, prev, ldp, t0)));
-      m1 = fmaxf(m1, fabsf(xval(X, ldx, s, k + st, c, prev, ldp, t0)));
-      m2 = fmaxf(m2, fabsf(xval(X, ldx, s, k + 2 * st, c, prev, ldp, t0)));
-      m3 = fmaxf(m3, fabsf(xval(X, ldx, s, k + 3 * st, c, prev, ldp, t0)));
+  const int rg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cc = c < cols ? c : cols - 1;
+  float m[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) m[u] = 0.f;
+  const int64_t st = (int64_t)gridDim.y * 4;
+  for (int64_t k = blockIdx.y * 4 + rg; k < rows; k += U * st) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t ku = k + u * st < rows ? k + u * st : k;   // (a repeated row)
+      float v = (float)X[ku * ldx + cc];
+      if (s) v *= s[ku];
+      m[u] = fmaxf(m[u], fabsf(v));
     }
-    for (; k < rows; k += st) m0 = fmaxf(m0, fabsf(xval(X, ldx, s, k, c, prev, ldp, t0)));
   }
-  part[rg][threadIdx.x & 63] = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
+#pragma unroll
+  for (int u = 1; u < U; ++u) m[0] = fmaxf(m[0], m[u]);
+  part[rg][threadIdx.x & 63] = m[0];
   __syncthreads();
-  // one atomic per column and workgroup
   if (rg == 0 && c < cols) {
     const int i = threadIdx.x;
-    const float m = fmaxf(fmaxf(part[0][i], part[1][i]), fmaxf(part[2][i], part[3][i]));
-    atomicMax(tmax + c, __float_as_uint(m));
+    const float v = fmaxf(fmaxf(part[0][i], part[1][i]), fmaxf(part[2][i], part[3][i]));
+    atomicMax(tmax + c, __float_as_uint(v));
   }
 }
 
-// t[c] = tmax[c] / 448 (1 for a zero column)
-__global__ __launch_bounds__(256) void colscale_kernel(const uint32_t* tmax, int cols, float* t) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= cols) return;
-  const float m = __uint_as_float(tmax[c]);
-  t[c] = m > 0.f ? m / 448.f : 1.f;
-}
+// Xt[c][k] = e4m3(X'(k, c) / t[c]), t from tmax (and written by the first k
+// block); padding k in [rows, ldo) zero (ldo a multiple of 16).  One tile of
+// 128 k x 64 columns per workgroup: s_k X(k, c) goes through LDS (read with c
+// contiguous), then a thread forms four codes of consecutive k (one word of
+// prev and of Xt), so every access is coalesced.  With rmax (RMAX), the column
+// maxima of what these codes leave go there: the second term needs no pass
+// of its own for them (and the workgroup takes ENC_TILES tiles, for fewer
+// atomics on the few column words: 286 -> 117 us at 65536 x 576).
+constexpr int TK = 128, TC = 64;
+constexpr int ENC_TILES = 4;
 
-// Xt[c][k] = e4m3(X'(k, c) / t[c]); padding k in [rows, ldo) zero.  One 64 x
-// 64 tile per workgroup: s_k X(k, c) goes through LDS (read with c
-// contiguous), the residual term and the code are formed with k contiguous
-// (the reads of prev and the writes of Xt), so all three are coalesced.  The
-// arithmetic is xval's, in its order.
-constexpr int TT = 64;
-
-template <typename TX>
+template <typename TX, bool PREV, bool RMAX>
 __global__ __launch_bounds__(256) void encode_kernel(const TX* __restrict__ X, int64_t ldx,
-                                                     int64_t rows, int cols, const float* s,
-                                                     const uint8_t* prev, int64_t ldp,
-                                                     const float* t0, const float* t,
-                                                     uint8_t* __restrict__ Xt, int64_t ldo) {
-  __shared__ float tile[TT][TT + 1];
-  const int64_t k0 = (int64_t)blockIdx.x * TT;
-  const int c0 = blockIdx.y * TT;
-  const int lo = threadIdx.x & 63, hi = threadIdx.x >> 6;
-  for (int i = hi; i < TT; i += 4) {
-    const int64_t k = k0 + i;
-    const int c = c0 + lo;
-    float v = 0.f;
-    if (k < rows && c < cols) {
-      v = (float)X[k * ldx + c];
+                                                     int64_t rows, int cols,
+                                                     const float* __restrict__ s,
+                                                     const uint8_t* __restrict__ prev,
+                                                     int64_t ldp, const float* __restrict__ t0,
+                                                     const uint32_t* __restrict__ tmax, float* t,
+                                                     uint8_t* __restrict__ Xt, int64_t ldo,
+                                                     uint32_t* rmax) {
+  __shared__ float tile[TK][TC + 1];
+  constexpr int CI = TC / 8;                      // columns per thread
+  const int c0 = blockIdx.y * TC;
+  const int lo = threadIdx.x & 63, hi = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int cl = min(c0 + lo, cols - 1);
+  const int kq = threadIdx.x & 31, cg = threadIdx.x >> 5;   // four k values, column group
+  if (blockIdx.x == 0 && hi == 0 && c0 + lo < cols) t[c0 + lo] = col_scale(tmax[c0 + lo]);
+  float m[CI];
+#pragma unroll
+  for (int x = 0; x < CI; ++x) m[x] = 0.f;
+  constexpr int NTILE = RMAX ? ENC_TILES : 1;
+  for (int ti = 0; ti < NTILE; ++ti) {
+    const int64_t k0 = ((int64_t)blockIdx.x * NTILE + ti) * TK;
+    if (k0 >= ldo) break;                         // (the whole workgroup)
+    if (ti > 0) __syncthreads();
+#pragma unroll 16
+    for (int i = hi; i < TK; i += 4) {
+      const int64_t k = min(k0 + i, rows - 1);    // (rows past the end are not used)
+      float v = (float)X[k * ldx + cl];
       if (s) v *= s[k];
+      tile[i][lo] = v;
     }
-    tile[i][lo] = v;
+    __syncthreads();
+    const int64_t k = k0 + 4 * kq;
+#pragma unroll
+    for (int x = 0; x < CI; ++x) {
+      const int i = cg + 8 * x, c = c0 + i;
+      if (c >= cols) break;
+      const float tc = col_scale(tmax[c]);
+      const float p0 = PREV ? t0[c] : 0.f;
+      uint32_t pw = 0u;
+      if (PREV && k < ldp) pw = *reinterpret_cast<const uint32_t*>(prev + (int64_t)c * ldp + k);
+      float v[4], y[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = tile[4 * kq + j][i];
+      if (PREV) {
+        v[0] = residual<0>(v[0], p0, pw);
+        v[1] = residual<1>(v[1], p0, pw);
+        v[2] = residual<2>(v[2], p0, pw);
+        v[3] = residual<3>(v[3], p0, pw);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        v[j] = k + j < rows ? v[j] : 0.f;
+        y[j] = v[j] / tc;
+      }
+      const uint32_t code = e4m3_pack(y);
+      if (k < ldo) *reinterpret_cast<uint32_t*>(Xt + (int64_t)c * ldo + k) = code;
+      if (RMAX) {
+        m[x] = fmaxf(m[x], fmaxf(fabsf(residual<0>(v[0], tc, code)),
+                                 fabsf(residual<1>(v[1], tc, code))));
+        m[x] = fmaxf(m[x], fmaxf(fabsf(residual<2>(v[2], tc, code)),
+                                 fabsf(residual<3>(v[3], tc, code))));
+      }
+    }
   }
-  __syncthreads();
-  for (int i = hi; i < TT; i += 4) {
-    const int c = c0 + i;
-    const int64_t k = k0 + lo;
-    if (c >= cols || k >= ldo) continue;
-    uint8_t code = 0;
-    if (k < rows) {
-      float v = tile[lo][i];
-      if (prev) v -= t0[c] * e4m3_to_float(prev[(int64_t)c * ldp + k]);
-      code = e4m3_from_float(v / t[c]);
+  if (RMAX) {
+#pragma unroll
+    for (int x = 0; x < CI; ++x) {
+      const int c = c0 + cg + 8 * x;
+#pragma unroll
+      for (int d = 1; d < 32; d <<= 1) m[x] = fmaxf(m[x], __shfl_xor(m[x], d, 32));
+      if (kq == 0 && c < cols) atomicMax(rmax + c, __float_as_uint(m[x]));
     }
-    Xt[(int64_t)c * ldo + k] = code;
   }
 }
 
@@ -163,23 +191,33 @@ __global__ void zero_u32_kernel(uint32_t* p, int n) {
 template <typename TX>
 hipError_t quant_x(const TX* X, int64_t ldx, int64_t rows, int cols, const float* s,
                    const uint8_t* prev, int64_t ldp, const float* t0, uint8_t* Xt, int64_t ldo,
-                   float* t, uint32_t* tmax, hipStream_t st) {
-  const unsigned cb = (unsigned)cdiv(cols, 256);
-  hipLaunchKernelGGL(zero_u32_kernel, dim3(cb), dim3(256), 0, st, tmax, cols);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const unsigned gx = (unsigned)cdiv(cols, 64);
-  int64_t gy = cdiv(rows, 256);
-  if (gy > 256) gy = 256;
-  if (gy < 1) gy = 1;
-  hipLaunchKernelGGL(colmax_kernel<TX>, dim3(gx, (unsigned)gy), dim3(256), 0, st, X, ldx, rows,
-                     cols, s, prev, ldp, t0, tmax);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(colscale_kernel, dim3(cb), dim3(256), 0, st, tmax, cols, t);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const dim3 grid((unsigned)cdiv(ldo, TT), (unsigned)cdiv(cols, TT));
-  hipLaunchKernelGGL(encode_kernel<TX>, grid, dim3(256), 0, st, X, ldx, rows, cols, s, prev, ldp,
-                     t0, t, Xt, ldo);
+                   float* t, uint32_t* tmax, uint32_t* rmax, hipStream_t st) {
+  hipError_t e;
+  if (!prev) {
+    const unsigned cb = (unsigned)cdiv(cols, 256);
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(cb), dim3(256), 0, st, tmax, cols);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (rmax) {
+      hipLaunchKernelGGL(zero_u32_kernel, dim3(cb), dim3(256), 0, st, rmax, cols);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    const unsigned gx = (unsigned)cdiv(cols, 64);
+    int64_t gy = cdiv(rows, 128);
+    if (gy > 256) gy = 256;
+    hipLaunchKernelGGL(colmax_kernel<TX>, dim3(gx, (unsigned)gy), dim3(256), 0, st, X, ldx, rows,
+                       cols, s, tmax);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const dim3 grid((unsigned)cdiv(ldo, rmax ? TK * ENC_TILES : TK), (unsigned)cdiv(cols, TC));
+  if (prev)
+    hipLaunchKernelGGL((encode_kernel<TX, true, false>), grid, dim3(256), 0, st, X, ldx, rows, cols,
+                       s, prev, ldp, t0, tmax, t, Xt, ldo, nullptr);
+  else if (rmax)
+    hipLaunchKernelGGL((encode_kernel<TX, false, true>), grid, dim3(256), 0, st, X, ldx, rows, cols,
+                       s, nullptr, 0, nullptr, tmax, t, Xt, ldo, rmax);
+  else
+    hipLaunchKernelGGL((encode_kernel<TX, false, false>), grid, dim3(256), 0, st, X, ldx, rows,
+                       cols, s, nullptr, 0, nullptr, tmax, t, Xt, ldo, nullptr);
   return hipGetLastError();
 }
 
@@ -212,13 +250,14 @@ hipError_t launch_gemm_f8(bool trans, const uint8_t* A, int64_t lda, const uint8
 hipError_t launch_quant_x_f8(bool x_f32, const void* X, int64_t ldx, int64_t rows, int cols,
                              const float* rowscale, const uint8_t* prev, int64_t ldp,
                              const float* t0, uint8_t* Xt, int64_t ldo, float* t, uint32_t* tmax,
-                             hipStream_t s) {
+                             uint32_t* rmax, hipStream_t s) {
   if (rows <= 0 || cols <= 0) return hipSuccess;
+  if (ldo % 16 || (prev && ldp % 16)) return hipErrorInvalidValue;   // whole words of codes
   if (x_f32)
     return quant_x(static_cast<const float*>(X), ldx, rows, cols, rowscale, prev, ldp, t0, Xt, ldo,
-                   t, tmax, s);
+                   t, tmax, rmax, s);
   return quant_x(static_cast<const double*>(X), ldx, rows, cols, rowscale, prev, ldp, t0, Xt, ldo,
-                 t, tmax, s);
+                 t, tmax, rmax, s);
 }
 
 }  // namespace rsvd

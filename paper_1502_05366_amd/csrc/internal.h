@@ -67,13 +67,15 @@ hipError_t launch_gemm_f8(bool trans, const uint8_t* A, int64_t lda, const uint8
                           int64_t ldc, int64_t M, int64_t K, int64_t L, int ncu, void* part,
                           size_t part_cap, bool accumulate, hipStream_t s);
 // Xt[c][k] = e4m3(X'(k, c) / t[c]), t[c] = max_k |X'(k, c)| / 448, with X'(k, c)
-// = rowscale[k] X(k, c) (rowscale may be null), or with prev (the codes of a
-// first term, ld ldp, scales t0) the residual X'(k, c) - t0[c] dec(prev[c][k]).
-// tmax: cols words of scratch.
+// = rowscale[k] X(k, c) (rowscale may be null).  tmax: cols words of scratch.
+// With rmax (cols words; may be null) the column maxima of the residual
+// X' - t dec(Xt) are left there, for the second term: called with prev (the
+// codes of the first term, ld ldp, scales t0) and tmax = that rmax, it encodes
+// the residual X'(k, c) - t0[c] dec(prev[c][k]).
 hipError_t launch_quant_x_f8(bool x_f32, const void* X, int64_t ldx, int64_t rows, int cols,
                              const float* rowscale, const uint8_t* prev, int64_t ldp,
                              const float* t0, uint8_t* Xt, int64_t ldo, float* t, uint32_t* tmax,
-                             hipStream_t s);
+                             uint32_t* rmax, hipStream_t s);
 // Storage formats from an FP64 A: BF16 bit patterns (nearest, ties to even)
 // and FP8 E4M3 codes with per-column FP32 scales.
 hipError_t launch_quantize_bf16(const double* A, int64_t lda, int64_t m, int64_t n, uint16_t* Q,

@@ -135,7 +135,7 @@ struct F8Bufs {
   const float* ascale = nullptr;   // n column scales of A
   uint8_t* xt = nullptr;           // 2 x lp x rup(max(m, n), 16) codes (two terms)
   float* t = nullptr;              // 2 x lp column scales of the two terms
-  uint32_t* tmax = nullptr;        // lp words
+  uint32_t* tmax = nullptr;        // 2 x lp words (column maxima of the two terms)
 };
 
 // buffers of one orth (CholeskyQR2) call
@@ -249,7 +249,7 @@ size_t layout(const Shape& s, void* base, Bufs* out) {
   if (s.f8) {
     b.f8.xt = a.take<uint8_t>((size_t)2 * s.lp * rup(std::max(s.m, s.n), 16));
     b.f8.t = a.take<float>((size_t)2 * s.lp);
-    b.f8.tmax = a.take<uint32_t>((size_t)s.lp);
+    b.f8.tmax = a.take<uint32_t>((size_t)2 * s.lp);
   }
   b.ob = take_orth(a, rmax, s.lp, max_part(s));
   if (s.ops & RSVD_OP_SVD) {
@@ -434,14 +434,15 @@ hipError_t pass(Ctx& c, int atype, bool trans, int64_t m, int64_t n, int l, cons
     const float* rs = trans ? c.f8.ascale : nullptr;     // epilogue row scale for A^T X
     uint8_t* x0 = c.f8.xt;
     uint8_t* x1 = c.f8.xt + (size_t)lp * ldt;
+    uint32_t* rmax = c.f8.tmax + lp;
     RSVD_TRY(launch_quant_x_f8(true, X, ldx, K, l, xs, nullptr, 0, nullptr, x0, ldt, c.f8.t,
-                               c.f8.tmax, c.st));
+                               c.f8.tmax, split ? rmax : nullptr, c.st));
     RSVD_TRY(launch_gemm_f8(trans, static_cast<const uint8_t*>(A), lda, x0, ldt, c.f8.t, rs,
                             static_cast<float*>(Y), ldy, M, K, l, ncu, part, part_bytes, false,
                             c.st));
     if (!split) return hipSuccess;
-    RSVD_TRY(launch_quant_x_f8(true, X, ldx, K, l, xs, x0, ldt, c.f8.t, x1, ldt, c.f8.t + lp,
-                               c.f8.tmax, c.st));
+    RSVD_TRY(launch_quant_x_f8(true, X, ldx, K, l, xs, x0, ldt, c.f8.t, x1, ldt, c.f8.t + lp, rmax,
+                               nullptr, c.st));
     return launch_gemm_f8(trans, static_cast<const uint8_t*>(A), lda, x1, ldt, c.f8.t + lp, rs,
                           static_cast<float*>(Y), ldy, M, K, l, ncu, part, part_bytes, true, c.st);
   }
@@ -1566,7 +1567,7 @@ size_t f8_pass_layout(int trans, int64_t m, int64_t n, int64_t l, void* base, F8
   F8Bufs b;
   b.xt = a.take<uint8_t>((size_t)2 * lp * rup(K, 16));
   b.t = a.take<float>((size_t)2 * lp);
-  b.tmax = a.take<uint32_t>((size_t)lp);
+  b.tmax = a.take<uint32_t>((size_t)2 * lp);
   void* pp = a.take<char>(pb);
   if (f) *f = b;
   if (part) *part = pp;
