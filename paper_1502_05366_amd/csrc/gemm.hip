@@ -20,6 +20,7 @@
 // global loads: rows of A (or of A^T's storage) are read along their
 // contiguous dimension, so every byte of A is read from HBM once per pass.
 #include "common.h"
+#include "gemm_reg.h"
 #include "internal.h"
 
 namespace rsvd {
@@ -252,9 +253,9 @@ __global__ __launch_bounds__(NT) void gemm_sk_kernel(GemmArgs g) {
 constexpr int FIX_CHUNK = 1024;
 constexpr int FIX_CHUNK_FEW = 256;
 
-template <typename TC, typename TO, int CBW>
+template <typename TC, typename TO, int NB>
 __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs g) {
-  constexpr int BN = 32 * CBW;
+  constexpr int BN = 16 * NB;
   const int64_t tile = blockIdx.x;
   const int64_t ufirst = tile * g.KI;
   const int64_t ulast = ufirst + g.KI - 1;
@@ -295,21 +296,62 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs g) {
   }
 }
 
+// adds the partial tiles of the split tiles (none with one workgroup per
+// tile: every range is a whole tile)
+template <typename TC, typename TO, int NB>
+hipError_t fixup(const GemmArgs& g, hipStream_t s) {
+  const int64_t T = g.U / g.KI;
+  if (g.G == T) return hipSuccess;
+  unsigned nch = (unsigned)cdiv(BM * 16 * NB, FIX_CHUNK);
+  if (T * nch < 4 * 256) nch = (unsigned)cdiv(BM * 16 * NB, FIX_CHUNK_FEW);
+  hipLaunchKernelGGL((gemm_fixup_kernel<TC, TO, NB>), dim3((unsigned)T, nch), dim3(256), 0, s, g);
+  return hipGetLastError();
+}
+
 template <typename TA, typename TX, typename TC, typename TO, bool TRANS, int CBW>
 hipError_t run(const GemmArgs& g, hipStream_t s) {
   hipLaunchKernelGGL((gemm_sk_kernel<TA, TX, TC, TO, TRANS, CBW>), dim3(g.G), dim3(NT), 0, s, g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // with one workgroup per tile every range is a whole tile: no fix-up
-  const int64_t T = g.U / g.KI;
-  if (g.G != T) {
-    unsigned nch = (unsigned)cdiv(BM * 32 * CBW, FIX_CHUNK);
-    if (T * nch < 4 * 256) nch = (unsigned)cdiv(BM * 32 * CBW, FIX_CHUNK_FEW);
-    hipLaunchKernelGGL((gemm_fixup_kernel<TC, TO, CBW>), dim3((unsigned)T, nch), dim3(256), 0, s,
-                       g);
-    e = hipGetLastError();
+  return fixup<TC, TO, 2 * CBW>(g, s);
+}
+
+// the kernel with A in registers (gemm_reg.h), NB column blocks per tile
+template <typename T, bool TRANS, int NB>
+hipError_t run_reg(const GemmArgs& g, hipStream_t s) {
+  static_assert(gemmreg::BM == BM && gemmreg::BK == BK, "the plan's tiles");
+  gemmreg::Args a;
+  a.A = g.A; a.lda = g.lda; a.X = g.X; a.ldx = g.ldx; a.C = g.C; a.ldc = g.ldc;
+  a.M = g.M; a.K = g.K; a.L = g.L;
+  a.nct = g.nct; a.KI = g.KI; a.U = g.U; a.G = g.G; a.part = g.part;
+  hipLaunchKernelGGL((gemmreg::kernel<T, TRANS, NB>), dim3((unsigned)g.G), dim3(gemmreg::NT), 0, s,
+                     a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return fixup<T, T, NB>(g, s);
+}
+
+template <typename T, bool TRANS>
+hipError_t dispatch_reg(const GemmArgs& g, int nb, hipStream_t s) {
+  switch (nb) {
+    case 1: return run_reg<T, TRANS, 1>(g, s);
+    case 2: return run_reg<T, TRANS, 2>(g, s);
+    case 3: return run_reg<T, TRANS, 3>(g, s);
+    case 4: return run_reg<T, TRANS, 4>(g, s);
+    case 5: return run_reg<T, TRANS, 5>(g, s);
+    case 6: return run_reg<T, TRANS, 6>(g, s);
+    case 7: return run_reg<T, TRANS, 7>(g, s);
+    case 8: return run_reg<T, TRANS, 8>(g, s);
+    case 9: return run_reg<T, TRANS, 9>(g, s);
+    case 10: return run_reg<T, TRANS, 10>(g, s);
+    case 11: return run_reg<T, TRANS, 11>(g, s);
+    case 12: return run_reg<T, TRANS, 12>(g, s);
+    case 13: return run_reg<T, TRANS, 13>(g, s);
+    case 14: return run_reg<T, TRANS, 14>(g, s);
+    case 15: return run_reg<T, TRANS, 15>(g, s);
+    case 16: return run_reg<T, TRANS, 16>(g, s);
+    default: return hipErrorInvalidValue;
   }
-  return e;
 }
 
 template <typename TA, typename TX, typename TC, typename TO, bool TRANS>
@@ -389,6 +431,23 @@ hipError_t launch_gemm(GemmTypes ty, bool trans, const void* A, int64_t lda, con
   g.A = A; g.lda = lda; g.X = X; g.ldx = ldx; g.C = C; g.ldc = ldc;
   g.M = M; g.K = K; g.L = L;
   g.nct = p.nct; g.KI = p.KI; g.U = p.U; g.G = p.G; g.part = part;
+  if ((ty == GEMM_DDDD || ty == GEMM_FFFF) && p.KI >= 2 &&
+      (ty == GEMM_FFFF || trans || p.cbw > 1)) {
+    // A in registers, except the FP64 A X of up to 32 columns: bound by reading A,
+    // it has more loads in flight in the tile kernel (20000 x 10000, l = 30:
+    // 373 us there, 397 here; A^T X 353 there, 307 here)
+    // (several column tiles keep the plan's widths, which the work ranges follow)
+    const int nb = p.nct == 1 ? (int)cdiv(L, 16) : 2 * p.cbw;
+    if (ty == GEMM_FFFF && p.G != p.nrt * p.nct) {
+      // two workgroups per compute unit
+      const int64_t G = p.cbw <= 2 ? p.G : 2 * p.G;
+      if (G <= p.U / 16 && (size_t)(2 * G) * (size_t)(BM * 16 * nb) * sizeof(float) <= part_cap)
+        g.G = G;
+    }
+    if (ty == GEMM_DDDD)
+      return trans ? dispatch_reg<double, true>(g, nb, s) : dispatch_reg<double, false>(g, nb, s);
+    return trans ? dispatch_reg<float, true>(g, nb, s) : dispatch_reg<float, false>(g, nb, s);
+  }
   switch (ty) {
     case GEMM_DDDD: return dispatch_trans<double, double, double, double>(g, trans, p.cbw, s);
     case GEMM_FFFF: return dispatch_trans<float, float, float, float>(g, trans, p.cbw, s);
