@@ -431,11 +431,9 @@ hipError_t launch_gemm(GemmTypes ty, bool trans, const void* A, int64_t lda, con
   g.A = A; g.lda = lda; g.X = X; g.ldx = ldx; g.C = C; g.ldc = ldc;
   g.M = M; g.K = K; g.L = L;
   g.nct = p.nct; g.KI = p.KI; g.U = p.U; g.G = p.G; g.part = part;
-  if ((ty == GEMM_DDDD || ty == GEMM_FFFF) && p.KI >= 2 &&
-      (ty == GEMM_FFFF || trans || p.cbw > 1)) {
-    // A in registers, except the FP64 A X of up to 32 columns: bound by reading A,
-    // it has more loads in flight in the tile kernel (20000 x 10000, l = 30:
-    // 373 us there, 397 here; A^T X 353 there, 307 here)
+  // products of one type: A in registers (gemm_reg.h), faster at every width
+  // measured (there); its loads need one k-step before the last
+  if ((ty == GEMM_DDDD || ty == GEMM_FFFF) && p.KI >= 2) {
     // (several column tiles keep the plan's widths, which the work ranges follow)
     const int nb = p.nct == 1 ? (int)cdiv(L, 16) : 2 * p.cbw;
     if (ty == GEMM_FFFF && p.G != p.nrt * p.nct) {
