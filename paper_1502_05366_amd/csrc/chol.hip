@@ -4,27 +4,31 @@
 // applied twice (CholeskyQR2) so that Q is orthonormal to working precision.
 //
 // Kernels here:
-//  * chol_kernel: one workgroup factors an lp x lp Gram matrix (lp <= 256)
+//  * chol_factor: one workgroup factors an lp x lp Gram matrix (lp <= 256)
 //    held in 16x16 matrix-core accumulator tiles (right-looking, block size
 //    16, one-step lookahead).  It writes R (upper triangular, zero below), the inverses
 //    of its 16x16 diagonal blocks, and a flag per column.  A column whose
 //    Schur pivot is not above eta * G_jj (numerically dependent on the
 //    columns before it) gets a unit row in R, so it is removed from the
 //    factorization of the later columns and can be replaced afterwards.
-//  * chol_ni_kernel: the factor of the second pass's Gram matrix, which is
-//    I + E with E of the order of the unit roundoff times cond(Y)^2.  With
-//    R = I + F (F upper triangular), R^T R = I + E reads F = Phi(E - F^T F),
-//    Phi taking the strict upper triangle and half the diagonal, so
-//    F = Phi(E) + O(||E||^2) and R^{-1} = I - F + O(||F||^2).  When
-//    ||E||_F^2 <= NI_TAU2 (a quarter of the unit roundoff) both truncations
-//    sit below rounding.  The kernel writes R = I + Phi(E) with the inverses
-//    of its diagonal blocks and the parts of ||E||_F^2; chol_kernel adds the
-//    parts and returns at once when the test passes, and otherwise factors G
-//    as in the first pass, overwriting R.
+//  * the factor of the second pass's Gram matrix, which is I + E with E of the
+//    order of the unit roundoff times cond(Y)^2.  With R = I + F (F upper
+//    triangular), R^T R = I + E reads F = Phi(E - F^T F), Phi taking the strict
+//    upper triangle and half the diagonal, so F = Phi(E) + O(||E||^2) and
+//    R^{-1} = I - F + O(||F||^2).  When ||E||_F^2 <= NI_TAU2 (a quarter of the
+//    unit roundoff) both truncations sit below rounding: the tiles of R = I +
+//    Phi(E) are written where the tiles of G are summed, with the parts of
+//    ||E||_F^2, and the factorization runs only when the test fails.
+//  * gram_kernel sums Y^T Y over row ranges into partial tiles;
+//    gram_chol_kernel, one workgroup per tile, adds them in a fixed order, and
+//    its last workgroup to finish tests and factors G: separate kernels for the
+//    sums, the test and the factorization cost a launch of 4 - 5 us each where
+//    the work is shorter.  (The last workgroup of gram_kernel doing all of it is
+//    slower even at l = 30: 28 us against 8 + 9.)
 //  * trsm_kernel: Q = Y R^{-1} for a tall Y, one wave per 16 rows, column
-//    block by column block (Q_c = (Y_c - sum_{b<c} Q_b R_bc) R_cc^{-1}).
-//  * replace_kernel: overwrites flagged columns of Q with fresh Gaussian
-//    vectors (Philox stream 7) scaled to unit expected norm.
+//    block by column block (Q_c = (Y_c - sum_{b<c} Q_b R_bc) R_cc^{-1}); a
+//    flagged column of Q gets fresh Gaussian numbers (Philox stream 7) scaled to
+//    unit expected norm instead.
 //  * trmm_kernel: R = R2 R1 for the two passes.
 #include <type_traits>
 
@@ -34,7 +38,6 @@
 namespace rsvd {
 namespace {
 
-constexpr int NI_NT = 256;
 constexpr double NI_TAU2 = 2.5e-17;   // bound on ||G - I||_F^2 (about a quarter of 2^-52)
 // ||G - I||_F^2 of the second Gram below which an FP32 basis is the first
 // pass rounded to FP32: (2^-30)^2, far below the FP32 unit roundoff 2^-24
@@ -79,7 +82,7 @@ __device__ __forceinline__ d4 load_gtile(const double* G, int64_t ldg, int l, in
     // one load per element (clamped address), no branches
     const bool in = row < l && col < l;
     const int64_t off = in ? (int64_t)min(row, col) * ldg + max(row, col) : 0;
-    const double g = G[off];
+    const double g = ld_agent(G + off);   // (written by other workgroups of this launch)
     t[v] = in ? g : ((row == col) ? 1.0 : 0.0);
   }
   return t;
@@ -100,21 +103,11 @@ __device__ __forceinline__ d4 load_gtile(const double* G, int64_t ldg, int l, in
 // The panel lives in LDS (16 x lp, one buffer: phase 2 of a step writes it
 // after phase 1 has read the previous one).
 template <int NW, int TPW>
-__global__ __launch_bounds__(64 * NW) void chol_kernel(const double* __restrict__ G, int64_t ldg,
-                                                       int l, int lp, double eta,
-                                                       double* __restrict__ R, int64_t ldr,
-                                                       double* __restrict__ Rdinv,
-                                                       int32_t* __restrict__ dep, int32_t* info,
-                                                       const double* __restrict__ ni_part) {
+__device__ __forceinline__ void chol_factor(const double* G, int64_t ldg, int l, int lp,
+                                            double eta, double* R, int64_t ldr, double* Rdinv,
+                                            int32_t* dep, int32_t* info) {
   constexpr int NT = 64 * NW, NU = NW - 1;
   const int nb = lp / 16;
-  if (ni_part != nullptr) {
-    // the near-identity test: the blocks' parts of ||G - I||_F^2, added in a
-    // fixed order by every wave (each lane holds at most one part)
-    const int ln = threadIdx.x & 63;
-    const double e2 = wave_allsum(ln < nb ? ni_part[ln] : 0.0);
-    if (e2 <= NI_TAU2) return;   // false for NaN
-  }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
@@ -128,7 +121,8 @@ __global__ __launch_bounds__(64 * NW) void chol_kernel(const double* __restrict_
   __shared__ double diag0[256];
   __shared__ int depblk[16];
 
-  for (int j = tid; j < lp; j += NT) diag0[j] = (j < l) ? G[(int64_t)j * ldg + j] : 1.0;
+  for (int j = tid; j < lp; j += NT)
+    diag0[j] = (j < l) ? ld_agent(G + (int64_t)j * ldg + j) : 1.0;
   // zero the strictly lower part of R
   for (int r = 1 + wave; r < lp; r += NW)
     for (int c = lane; c < r; c += 64) R[(int64_t)r * ldr + c] = 0.0;
@@ -320,56 +314,26 @@ __global__ __launch_bounds__(64 * NW) void chol_kernel(const double* __restrict_
   }
 }
 
-// Workgroup c takes rows 16c .. 16c+15: it writes those rows of R = I + Phi(G - I)
-// (zero below the diagonal, identity in the padding), the inverse
-// I - F_cc + F_cc^2 of the diagonal block, clear flags for those columns, and
-// its part of ||G - I||_F^2 (upper triangle, off-diagonal entries twice) to
-// part[c].  The writes are speculative: chol_kernel adds the parts in order
-// and, when the sum exceeds NI_TAU2, overwrites all of them.
-__global__ __launch_bounds__(NI_NT) void chol_ni_kernel(const double* __restrict__ G, int64_t ldg,
-                                                        int l, int lp, double* __restrict__ R,
-                                                        int64_t ldr, double* __restrict__ Rdinv,
-                                                        int32_t* __restrict__ dep,
-                                                        double* __restrict__ part) {
-  constexpr int NW = NI_NT / 64;
-  __shared__ double red[NW];
-  __shared__ double Fd[16 * 17];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = blockIdx.x;
-  double s = 0.0;
-  // wave w takes rows 16c + w, 16c + w + NW, ...; lanes run along the row
-  for (int ii = wave; ii < 16; ii += NW) {
-    const int i = c * 16 + ii;
-    const double* gr = G + (int64_t)i * ldg;
-    double* rr = R + (int64_t)i * ldr;
-    for (int j = lane; j < lp; j += 64) {
-      double f = 0.0;
-      if (i < l && j < l && i <= j) {
-        const double x = gr[j] - (i == j ? 1.0 : 0.0);
-        s = fma((i == j ? 1.0 : 2.0) * x, x, s);
-        f = (i == j) ? 0.5 * x : x;
-      }
-      rr[j] = (i == j ? 1.0 : 0.0) + f;
-      if ((j >> 4) == c) Fd[ii * 17 + (j & 15)] = f;
-    }
+// Normal number t of a Philox stream.  A flagged column j of Q (M rows) is
+// replaced by N(0, 1/M) entries from stream 7, number j*M + i for row i, batch =
+// the orth call.
+__device__ __forceinline__ double normal_at(uint32_t k0, uint32_t k1, uint32_t sid, uint32_t batch,
+                                            uint64_t t) {
+  uint32_t c0 = (uint32_t)(t >> 1), c1 = (uint32_t)(t >> 33), c2 = sid, c3 = batch;
+  const uint32_t PM0 = 0xD2511F53u, PM1 = 0xCD9E8D57u, PW0 = 0x9E3779B9u, PW1 = 0xBB67AE85u;
+#pragma unroll
+  for (int r = 0; r < 10; ++r) {
+    if (r > 0) { k0 += PW0; k1 += PW1; }
+    const uint32_t hi0 = __umulhi(PM0, c0), lo0 = PM0 * c0;
+    const uint32_t hi1 = __umulhi(PM1, c2), lo1 = PM1 * c2;
+    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
   }
-  s = wave_allsum(s);
-  if (lane == 0) red[wave] = s;
-  if (tid < 16 && c * 16 + tid < l) dep[c * 16 + tid] = 0;
-  __syncthreads();
-  if (tid == 0) {
-    double t = 0.0;
-    for (int w = 0; w < NW; ++w) t += red[w];
-    part[c] = t;
-  }
-  // inverse of the diagonal block: I - F_cc + F_cc^2
-  {
-    const int x = tid >> 4, y = tid & 15;
-    double f2 = 0.0;
-    for (int t = x; t <= y; ++t) f2 = fma(Fd[x * 17 + t], Fd[t * 17 + y], f2);
-    Rdinv[(int64_t)c * 256 + x * 16 + y] = ((x == y) ? 1.0 : 0.0) - Fd[x * 17 + y] + f2;
-  }
+  const double a = (double)(c0 >> 5) * 67108864.0 + (double)(c1 >> 6);
+  const double b = (double)(c2 >> 5) * 67108864.0 + (double)(c3 >> 6);
+  const double u1 = (a + 1.0) * 0x1.0p-53, u2 = b * 0x1.0p-53;
+  const double r = sqrt(-2.0 * log(u1)), th = 6.283185307179586 * u2;
+  return (t & 1) ? r * sin(th) : r * cos(th);
 }
 
 // Q = Y R^{-1}: a workgroup of 4 waves takes 64 rows of Y (a wave 16),
@@ -389,7 +353,9 @@ __global__ __launch_bounds__(256) void trsm_kernel(const TY* __restrict__ Y, int
                                                    const double* __restrict__ R, int64_t ldr,
                                                    const double* __restrict__ Rdinv,
                                                    TQ* __restrict__ Q, int64_t ldq,
-                                                   const double* __restrict__ skip_part) {
+                                                   const double* __restrict__ skip_e2,
+                                                   const int32_t* __restrict__ dep, uint64_t seed,
+                                                   uint32_t call) {
   __shared__ double Rb[2][NB * 256];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -400,13 +366,9 @@ __global__ __launch_bounds__(256) void trsm_kernel(const TY* __restrict__ Y, int
   const bool rok = r < M;
   const TY* yr = Y + (rok ? r : 0) * ldy;
   TQ* qr = Q + (rok ? r : 0) * ldq;
-  if (skip_part) {
-    // ||Y^T Y - I||_F^2 from its parts (the same order on every thread, so
-    // the whole workgroup takes the same branch): when Y is orthonormal to
-    // within TRSM_SKIP2, Q = Y rounded to TQ
-    double e2 = 0.0;
-    for (int c = 0; c < nb; ++c) e2 += skip_part[c];
-    if (e2 <= TRSM_SKIP2) {
+  if (skip_e2) {
+    // when Y is orthonormal to within TRSM_SKIP2, Q = Y rounded to TQ
+    if (*skip_e2 <= TRSM_SKIP2) {
       for (int c = 0; c < nb; ++c) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -476,51 +438,19 @@ __global__ __launch_bounds__(256) void trsm_kernel(const TY* __restrict__ Y, int
       __syncthreads();
     }
   });
-}
-
-// Replace every flagged column j of Q (M rows) by N(0, 1/M) entries from
-// Philox stream 7, counter pair index = j*M + i for normal (i, j), batch = call.
-__device__ __forceinline__ double normal_at(uint32_t k0, uint32_t k1, uint32_t sid, uint32_t batch,
-                                            uint64_t t) {
-  uint32_t c0 = (uint32_t)(t >> 1), c1 = (uint32_t)(t >> 33), c2 = sid, c3 = batch;
-  const uint32_t PM0 = 0xD2511F53u, PM1 = 0xCD9E8D57u, PW0 = 0x9E3779B9u, PW1 = 0xBB67AE85u;
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r > 0) { k0 += PW0; k1 += PW1; }
-    const uint32_t hi0 = __umulhi(PM0, c0), lo0 = PM0 * c0;
-    const uint32_t hi1 = __umulhi(PM1, c2), lo1 = PM1 * c2;
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
-  }
-  const double a = (double)(c0 >> 5) * 67108864.0 + (double)(c1 >> 6);
-  const double b = (double)(c2 >> 5) * 67108864.0 + (double)(c3 >> 6);
-  const double u1 = (a + 1.0) * 0x1.0p-53, u2 = b * 0x1.0p-53;
-  const double r = sqrt(-2.0 * log(u1)), th = 6.283185307179586 * u2;
-  return (t & 1) ? r * sin(th) : r * cos(th);
-}
-
-template <typename TQ>
-__global__ __launch_bounds__(256) void replace_kernel(TQ* __restrict__ Q, int64_t ldq, int64_t M,
-                                                      int l, const int32_t* __restrict__ dep,
-                                                      uint64_t seed, uint32_t call) {
-  // the flagged columns, listed once per workgroup (usually none)
-  __shared__ int list[256];
-  __shared__ int cnt;
-  if (threadIdx.x == 0) cnt = 0;
-  __syncthreads();
-  for (int j = threadIdx.x; j < l; j += blockDim.x)
-    if (dep[j]) list[atomicAdd(&cnt, 1)] = j;
-  __syncthreads();
-  const int nd = cnt;
-  if (nd == 0) return;
-  const double scale = 1.0 / sqrt((double)M);
-  for (int q = 0; q < nd; ++q) {
-    const int j = list[q];
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < M;
-         i += (int64_t)gridDim.x * blockDim.x) {
-      const double z = normal_at((uint32_t)seed, (uint32_t)(seed >> 32), 7u, call,
-                                 (uint64_t)j * (uint64_t)M + (uint64_t)i);
-      Q[i * ldq + j] = (TQ)(z * scale);
+  if (dep != nullptr) {
+    // the flagged columns (usually none)
+    const double scale = 1.0 / sqrt((double)M);
+    for (int j0 = 0; j0 < l; j0 += 64) {
+      uint64_t flag = __ballot(j0 + lane < l && dep[min(j0 + lane, l - 1)] != 0);
+      for (; flag != 0; flag &= flag - 1) {
+        const int col = j0 + __builtin_ctzll(flag);
+        if (rok && lk == (col & 3)) {              // (the lane that stored this column above)
+          const double z = normal_at((uint32_t)seed, (uint32_t)(seed >> 32), 7u, call,
+                                     (uint64_t)col * (uint64_t)M + (uint64_t)r);
+          qr[col] = (TQ)(z * scale);
+        }
+      }
     }
   }
 }
@@ -557,6 +487,12 @@ __global__ __launch_bounds__(256) void trmm_kernel(const double* __restrict__ Am
 }
 
 __global__ void set_word_kernel(int32_t* w, int32_t v) { *w = v; }
+// the status words of a call and the sync words of its orths
+__global__ void reset_kernel(int32_t* info, OrthSync* s0, OrthSync* s1) {
+  if (threadIdx.x < 2) info[threadIdx.x] = 0;
+  if (threadIdx.x == 2 && s0) s0->ticket = 0u;
+  if (threadIdx.x == 3 && s1) s1->ticket = 0u;
+}
 
 // T = Y - T: the residual of a projection of Y (block orthonormalization)
 template <typename TY>
@@ -590,8 +526,8 @@ __global__ __launch_bounds__(64) void zero_dep_rows_kernel(double* __restrict__ 
 // stride 144 doubles, so the four row groups of a wave fall on different bank
 // halves), the next chunk is fetched into registers while the current one is
 // multiplied, and each tile accumulates on one wave's matrix cores.  Partial
-// tiles go to part[workgroup][slot]; gram_reduce_kernel adds a tile's
-// partials in workgroup order (deterministic).
+// tiles go to part[workgroup][slot]; gram_chol_kernel adds a tile's partials in
+// workgroup order (deterministic).
 constexpr int GR_NT = 512;
 constexpr int GR_NW = GR_NT / 64;
 constexpr int GR_SEG = 4;                   // column blocks per segment
@@ -604,6 +540,131 @@ struct GramPlan {
   int sa[GR_MAXG], sb[GR_MAXG];
   int off[GR_MAXG + 1];                     // first workgroup of each group
 };
+
+// What follows the sums of the partial tiles: the factorization.
+struct CholArgs {
+  double* G; int64_t ldg;
+  int l, lp;
+  double eta;
+  double* R; int64_t ldr;
+  double* Rdinv;
+  int32_t* dep;
+  int32_t* info;
+  double* parts;                  // NI: the tiles' parts of ||G - I||_F^2
+  OrthSync* sync;
+};
+
+// Tile t of G (512 threads): the sum over the workgroups of its group of their
+// partial tiles, in workgroup order (four interleaved chains added in a fixed
+// order; two halves of the workgroup take two chains each, sixteen loads in
+// flight).  NI: also the tile of R = I + Phi(G - I) (and the zeros below the
+// diagonal), the inverse I - F + F^2 of a diagonal block, clear flags and the
+// tile's part of ||G - I||_F^2 (off-diagonal entries twice).  What another
+// workgroup reads or rewrites in the same launch is stored past the L2.
+template <bool NI>
+__device__ __forceinline__ void reduce_tile(const double* part, const GramPlan& gp, int t,
+                                            const CholArgs& c) {
+  __shared__ double half1[256];
+  __shared__ double Fd[16 * 17];
+  __shared__ double red[4];
+  const int tid = threadIdx.x, e = tid & 255, h = tid >> 8;
+  const int a = tile_row(t, gp.nb), b = tile_col(t, gp.nb);
+  const int sa = a / GR_SEG, sb = b / GR_SEG;
+  const int g = sa * gp.nseg - sa * (sa - 1) / 2 + (sb - sa);
+  const int u = 4 * (a - GR_SEG * sa) + (b - GR_SEG * sb);
+  const int w0 = gp.off[g], ng = gp.off[g + 1] - w0;
+  const double* p = part + ((int64_t)w0 * 16 + u) * 256 + e;
+  auto ld = [&](int w) { return p[(int64_t)w * 4096]; };
+  constexpr int U = 8;
+  double s0 = 0.0, s1 = 0.0;
+  const int n4 = ng & ~3;                          // the interleaved part
+  for (int w = 0; w < n4; w += 4 * U) {
+    double x[U], y[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {                  // (past the end: the last one, not added)
+      const int v = min(w + 4 * i, n4 - 4) + 2 * h;
+      x[i] = ld(v);
+      y[i] = ld(v + 1);
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const bool in = w + 4 * i < n4;
+      s0 = in ? s0 + x[i] : s0;
+      s1 = in ? s1 + y[i] : s1;
+    }
+  }
+  if (h == 0 && n4 < ng) {
+    double x[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) x[i] = ld(min(n4 + i, ng - 1));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) s0 = n4 + i < ng ? s0 + x[i] : s0;
+  }
+  if (h == 1) half1[e] = s0 + s1;
+  __syncthreads();
+  const int i = e >> 4, j = e & 15;
+  const int gi = a * 16 + i, gj = b * 16 + j;
+  if (h == 0) {
+    const double x = (s0 + s1) + half1[e];
+    st_agent(c.G + (int64_t)gi * c.ldg + gj, x);
+    if constexpr (NI) {
+      const bool in = gi < c.l && gj < c.l && gi <= gj;
+      const double d = x - (gi == gj ? 1.0 : 0.0);
+      double s = in ? ((gi == gj ? 1.0 : 2.0) * d) * d : 0.0;
+      const double f = in ? (gi == gj ? 0.5 * d : d) : 0.0;
+      st_agent(c.R + (int64_t)gi * c.ldr + gj, (gi == gj ? 1.0 : 0.0) + f);
+      if (a == b) {
+        Fd[i * 17 + j] = f;
+        if (i == 0 && gj < c.l)
+          __hip_atomic_store(c.dep + gj, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      s = wave_allsum(s);
+      if ((tid & 63) == 0) red[tid >> 6] = s;
+    }
+  } else if constexpr (NI) {
+    if (a != b) st_agent(c.R + (int64_t)(b * 16 + i) * c.ldr + a * 16 + j, 0.0);
+  }
+  if constexpr (NI) {
+    __syncthreads();
+    if (tid == 0) st_agent(c.parts + t, ((red[0] + red[1]) + red[2]) + red[3]);
+    if (a == b && h == 0) {
+      double f2 = 0.0;
+      for (int q = i; q <= j; ++q) f2 = fma(Fd[i * 17 + q], Fd[q * 17 + j], f2);
+      st_agent(c.Rdinv + (int64_t)a * 256 + e, ((i == j) ? 1.0 : 0.0) - Fd[i * 17 + j] + f2);
+    }
+  }
+}
+
+// Whether this workgroup is the last of the launch to get here; what the others
+// stored past the L2 before is then visible to agent-scope loads.  (No
+// workgroup waits for another one.)
+__device__ __forceinline__ bool last_workgroup(OrthSync* sync) {
+  __shared__ int last;
+  stores_done();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t n =
+        __hip_atomic_fetch_add(&sync->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = n + 1u == gridDim.x;
+    if (last) st_agent_u32(&sync->ticket, 0u);       // for the next launch
+  }
+  __syncthreads();
+  return last != 0;
+}
+
+// the near-identity test (NI), or the factorization
+template <int TPW, bool NI>
+__device__ __forceinline__ void test_and_factor(const CholArgs& c) {
+  if constexpr (NI) {
+    const int nb = c.lp / 16, ntiles = nb * (nb + 1) / 2, ln = threadIdx.x & 63;
+    double e2 = 0.0;                               // (the same on every wave)
+    for (int t = ln; t < ntiles; t += 64) e2 += ld_agent(c.parts + t);
+    e2 = wave_allsum(e2);
+    if (threadIdx.x == 0) c.sync->e2 = e2;
+    if (e2 <= NI_TAU2) return;                     // false for NaN
+  }
+  chol_factor<8, TPW>(c.G, c.ldg, c.l, c.lp, c.eta, c.R, c.ldr, c.Rdinv, c.dep, c.info);
+}
 
 template <typename TY>
 __global__ __launch_bounds__(GR_NT) void gram_kernel(const TY* __restrict__ Y, int64_t ldy,
@@ -690,28 +751,13 @@ __global__ __launch_bounds__(GR_NT) void gram_kernel(const TY* __restrict__ Y, i
   }
 }
 
-// G_ab = sum over the workgroups of the group of (a, b) of their partial
-// tile, in workgroup order (four interleaved chains added in a fixed order).
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part,
-                                                          GramPlan gp, double* __restrict__ Gm,
-                                                          int64_t ldg) {
-  const int t = blockIdx.x, e = threadIdx.x;
-  const int a = tile_row(t, gp.nb), b = tile_col(t, gp.nb);
-  const int sa = a / GR_SEG, sb = b / GR_SEG;
-  const int g = sa * gp.nseg - sa * (sa - 1) / 2 + (sb - sa);
-  const int u = 4 * (a - GR_SEG * sa) + (b - GR_SEG * sb);
-  const int w0 = gp.off[g], ng = gp.off[g + 1] - w0;
-  const double* p = part + ((int64_t)w0 * 16 + u) * 256 + e;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  int w = 0;
-  for (; w + 4 <= ng; w += 4) {
-    s0 += p[(int64_t)(w + 0) * 4096];
-    s1 += p[(int64_t)(w + 1) * 4096];
-    s2 += p[(int64_t)(w + 2) * 4096];
-    s3 += p[(int64_t)(w + 3) * 4096];
-  }
-  for (; w < ng; ++w) s0 += p[(int64_t)w * 4096];
-  Gm[(int64_t)(a * 16 + (e >> 4)) * ldg + b * 16 + (e & 15)] = (s0 + s1) + (s2 + s3);
+// one workgroup per tile: the sums, and in the last one the factorization
+template <int TPW, bool NI>
+__global__ __launch_bounds__(GR_NT) void gram_chol_kernel(const double* __restrict__ part,
+                                                          GramPlan gp, CholArgs ca) {
+  reduce_tile<NI>(part, gp, blockIdx.x, ca);
+  if (!last_workgroup(ca.sync)) return;
+  test_and_factor<TPW, NI>(ca);
 }
 
 GramPlan plan_gram(int64_t rows, int lp, int ncu) {
@@ -750,41 +796,35 @@ size_t gram_part_bytes(int lp, int ncu) {
   return (size_t)2 * ncu * 16 * 256 * sizeof(double);
 }
 
-hipError_t launch_gram(bool y_f32, const void* Y, int64_t ldy, int64_t rows, int l, int lp,
-                       double* Gm, int64_t ldg, double* part, int ncu, hipStream_t s) {
+hipError_t launch_gram_chol(bool y_f32, const void* Y, int64_t ldy, int64_t rows, int l, int lp,
+                            double* Gm, int64_t ldg, double* part, int ncu, double eta, double* R,
+                            int64_t ldr, double* Rdinv, int32_t* dep, int32_t* info,
+                            OrthSync* sync, double* ni_parts, hipStream_t s) {
   if (lp > 256 || lp % 16) return hipErrorInvalidValue;
   const GramPlan gp = plan_gram(rows, lp, ncu);
+  const bool ni = ni_parts != nullptr;
+  CholArgs c;
+  c.G = Gm; c.ldg = ldg; c.l = l; c.lp = lp; c.eta = eta; c.R = R; c.ldr = ldr;
+  c.Rdinv = Rdinv; c.dep = dep; c.info = info; c.parts = ni_parts; c.sync = sync;
+  const int ntiles = gp.nb * (gp.nb + 1) / 2;
   if (y_f32)
-    hipLaunchKernelGGL(gram_kernel<float>, dim3(gp.total), dim3(GR_NT), 0, s, (const float*)Y,
-                       ldy, rows, l, gp, part);
+    hipLaunchKernelGGL(gram_kernel<float>, dim3(gp.total), dim3(GR_NT), 0, s, (const float*)Y, ldy,
+                       rows, l, gp, part);
   else
     hipLaunchKernelGGL(gram_kernel<double>, dim3(gp.total), dim3(GR_NT), 0, s, (const double*)Y,
                        ldy, rows, l, gp, part);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int ntiles = gp.nb * (gp.nb + 1) / 2;
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3(ntiles), dim3(256), 0, s, part, gp, Gm, ldg);
-  return hipGetLastError();
-}
-
-hipError_t launch_chol(const double* G, int64_t ldg, int l, int lp, double eta, double* R,
-                       int64_t ldr, double* Rdinv, int32_t* dep, int32_t* info, hipStream_t s,
-                       double* ni_part) {
-  if (lp > 256 || lp % 16) return hipErrorInvalidValue;
-  const int nb = lp / 16;
-  const int tiles = nb * (nb + 1) / 2;
-  if (ni_part != nullptr) {
-    hipLaunchKernelGGL(chol_ni_kernel, dim3(nb), dim3(NI_NT), 0, s, G, ldg, l, lp, R, ldr, Rdinv,
-                       dep, ni_part);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   // 8 waves: wave 0 factors the diagonal blocks, 7 hold the tiles (2 waves
   // per SIMD leave each up to 256 registers)
 #define RSVD_CHOL(T)                                                                        \
-  hipLaunchKernelGGL((chol_kernel<8, T>), dim3(1), dim3(512), 0, s, G, ldg, l, lp, eta, R, ldr, \
-                     Rdinv, dep, info, ni_part)
-  const int tpw = (int)cdiv(tiles, 7);
+  do {                                                                                      \
+    if (ni) hipLaunchKernelGGL((gram_chol_kernel<T, true>), dim3(ntiles), dim3(GR_NT), 0, s, part, \
+                               gp, c);                                                      \
+    else hipLaunchKernelGGL((gram_chol_kernel<T, false>), dim3(ntiles), dim3(GR_NT), 0, s, part, \
+                            gp, c);                                                         \
+  } while (0)
+  const int tpw = (int)cdiv(ntiles, 7);
   if (tpw <= 1) RSVD_CHOL(1);
   else if (tpw <= 2) RSVD_CHOL(2);
   else if (tpw <= 4) RSVD_CHOL(4);
@@ -798,56 +838,49 @@ hipError_t launch_chol(const double* G, int64_t ldg, int l, int lp, double eta, 
 template <int NB>
 hipError_t launch_trsm_nb(bool y_f32, bool q_f32, const void* Y, int64_t ldy, int64_t M, int l,
                           int lp, const double* R, int64_t ldr, const double* Rdinv, void* Q,
-                          int64_t ldq, const double* skip_part, hipStream_t s) {
+                          int64_t ldq, const double* skip_e2, const int32_t* dep, uint64_t seed,
+                          uint32_t call, hipStream_t s) {
   const dim3 grid((unsigned)cdiv(M, 64));
   if (!y_f32 && !q_f32)
     hipLaunchKernelGGL((trsm_kernel<double, double, NB>), grid, dim3(256), 0, s,
-                       (const double*)Y, ldy, M, l, lp, R, ldr, Rdinv, (double*)Q, ldq, skip_part);
+                       (const double*)Y, ldy, M, l, lp, R, ldr, Rdinv, (double*)Q, ldq, skip_e2, dep,
+                       seed, call);
   else if (y_f32 && q_f32)
     hipLaunchKernelGGL((trsm_kernel<float, float, NB>), grid, dim3(256), 0, s,
-                       (const float*)Y, ldy, M, l, lp, R, ldr, Rdinv, (float*)Q, ldq, skip_part);
+                       (const float*)Y, ldy, M, l, lp, R, ldr, Rdinv, (float*)Q, ldq, skip_e2, dep, seed,
+                       call);
   else if (y_f32 && !q_f32)
     hipLaunchKernelGGL((trsm_kernel<float, double, NB>), grid, dim3(256), 0, s,
-                       (const float*)Y, ldy, M, l, lp, R, ldr, Rdinv, (double*)Q, ldq, skip_part);
+                       (const float*)Y, ldy, M, l, lp, R, ldr, Rdinv, (double*)Q, ldq, skip_e2, dep,
+                       seed, call);
   else
     hipLaunchKernelGGL((trsm_kernel<double, float, NB>), grid, dim3(256), 0, s,
-                       (const double*)Y, ldy, M, l, lp, R, ldr, Rdinv, (float*)Q, ldq, skip_part);
+                       (const double*)Y, ldy, M, l, lp, R, ldr, Rdinv, (float*)Q, ldq, skip_e2, dep, seed,
+                       call);
   return hipGetLastError();
 }
 
 hipError_t launch_trsm(bool y_f32, bool q_f32, const void* Y, int64_t ldy, int64_t M, int l,
                        int lp, const double* R, int64_t ldr, const double* Rdinv, void* Q,
-                       int64_t ldq, hipStream_t s, const double* skip_part) {
+                       int64_t ldq, hipStream_t s, const double* skip_e2, const int32_t* dep,
+                       uint64_t seed, uint32_t call) {
   if (M <= 0) return hipSuccess;
   if (lp > 256 || lp % 16) return hipErrorInvalidValue;
   const int nb = lp / 16;
-  if (nb <= 2) 
+  if (nb <= 2)
     return launch_trsm_nb<2>(y_f32, q_f32, Y, ldy, M, l, lp, R, ldr, Rdinv, Q, ldq,
-                              skip_part, s);
-  if (nb <= 4) 
+                             skip_e2, dep, seed, call, s);
+  if (nb <= 4)
     return launch_trsm_nb<4>(y_f32, q_f32, Y, ldy, M, l, lp, R, ldr, Rdinv, Q, ldq,
-                              skip_part, s);
-  if (nb <= 8) 
+                             skip_e2, dep, seed, call, s);
+  if (nb <= 8)
     return launch_trsm_nb<8>(y_f32, q_f32, Y, ldy, M, l, lp, R, ldr, Rdinv, Q, ldq,
-                              skip_part, s);
+                             skip_e2, dep, seed, call, s);
   if (nb <= 12)
     return launch_trsm_nb<12>(y_f32, q_f32, Y, ldy, M, l, lp, R, ldr, Rdinv, Q, ldq,
-                              skip_part, s);
-  return launch_trsm_nb<16>(y_f32, q_f32, Y, ldy, M, l, lp, R, ldr, Rdinv, Q, ldq, skip_part,
-                            s);
-}
-
-hipError_t launch_replace(bool q_f32, void* Q, int64_t ldq, int64_t M, int l, const int32_t* dep,
-                          uint64_t seed, uint32_t call, hipStream_t s) {
-  if (l > 256) return hipErrorInvalidValue;
-  const int grid = (int)(cdiv(M, 256) < 1024 ? cdiv(M, 256) : 1024);
-  if (q_f32)
-    hipLaunchKernelGGL(replace_kernel<float>, dim3(grid), dim3(256), 0, s, (float*)Q, ldq, M, l,
-                       dep, seed, call);
-  else
-    hipLaunchKernelGGL(replace_kernel<double>, dim3(grid), dim3(256), 0, s, (double*)Q, ldq, M, l,
-                       dep, seed, call);
-  return hipGetLastError();
+                             skip_e2, dep, seed, call, s);
+  return launch_trsm_nb<16>(y_f32, q_f32, Y, ldy, M, l, lp, R, ldr, Rdinv, Q, ldq, skip_e2, dep,
+                            seed, call, s);
 }
 
 hipError_t launch_trmm_upper(const double* A, int64_t lda, const double* B, int64_t ldb,
@@ -861,6 +894,11 @@ hipError_t launch_trmm_upper(const double* A, int64_t lda, const double* B, int6
 
 hipError_t launch_set_word(int32_t* w, int32_t v, hipStream_t s) {
   hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(1), 0, s, w, v);
+  return hipGetLastError();
+}
+
+hipError_t launch_reset(int32_t* info, OrthSync* s0, OrthSync* s1, hipStream_t s) {
+  hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(64), 0, s, info, s0, s1);
   return hipGetLastError();
 }
 

@@ -84,32 +84,37 @@ hipError_t launch_bf16_residual(const float* X, int64_t ldx, int64_t rows, int c
 namespace rsvd {
 
 // ------------------------------------------------------------------ orth --
-// One Cholesky factorization of an lp x lp Gram matrix (lp <= 256, lp % 16 == 0,
-// only rows/columns < l are read).  R upper triangular (zero below), Rdinv the
+// Device words of one orth's buffers: the count of finished workgroups of the
+// launch in flight (zero between launches; launch_reset at the start of a
+// call) and ||G - I||_F^2 of the last second-pass Gram matrix.
+struct OrthSync {
+  double e2;
+  uint32_t ticket;
+};
+// info[0..1] = 0 and clear tickets (s0, s1 may be null)
+hipError_t launch_reset(int32_t* info, OrthSync* s0, OrthSync* s1, hipStream_t s);
+// G = Y^T Y (upper 16x16 tiles of an lp x lp matrix) in FP64 for a tall Y, sized
+// for ncu compute units (`part` holds gram_part_bytes(lp, ncu_cap) bytes for
+// any ncu <= ncu_cap), and its Cholesky factor (lp <= 256, lp % 16 == 0, only
+// rows/columns < l are read): R upper triangular (zero below), Rdinv the
 // inverses of its 16x16 diagonal blocks (lp/16 blocks of 256 doubles), dep[j]
-// = 1 for columns declared dependent (pivot <= eta * G_jj).  With ni_part
-// (lp/16 doubles of scratch), G is first taken as I + E: R = I + Phi(E) is
-// written by one workgroup per 16 rows together with the parts of
-// ||E||_F^2, and the full factorization returns at once when their sum is
-// below a quarter of the unit roundoff (and otherwise overwrites R).
-hipError_t launch_chol(const double* G, int64_t ldg, int l, int lp, double eta, double* R,
-                       int64_t ldr, double* Rdinv, int32_t* dep, int32_t* info, hipStream_t s,
-                       double* ni_part = nullptr);
-// G = Y^T Y (upper 16x16 tiles of an lp x lp matrix) in FP64 for a tall Y,
-// sized for ncu compute units; `part` holds gram_part_bytes(lp, ncu_cap)
-// bytes for any ncu <= ncu_cap.
+// = 1 for columns declared dependent (pivot <= eta * G_jj).  With ni_parts
+// (136 doubles of scratch), G is first taken as I + E: R = I + Phi(E) is
+// written, sync->e2 = ||E||_F^2, and the factorization runs (and overwrites R)
+// only when that is not below a quarter of the unit roundoff.
 size_t gram_part_bytes(int lp, int ncu_cap);
-hipError_t launch_gram(bool y_f32, const void* Y, int64_t ldy, int64_t rows, int l, int lp,
-                       double* Gm, int64_t ldg, double* part, int ncu, hipStream_t s);
-// Q = Y R^{-1} (M x l); Y and Q may be FP32 or FP64; arithmetic in FP64.
-// With skip_part (the lp/16 parts of ||Y^T Y - I||_F^2 left by the
-// near-identity Cholesky), Q = Y when their sum is at most 2^-60.
+hipError_t launch_gram_chol(bool y_f32, const void* Y, int64_t ldy, int64_t rows, int l, int lp,
+                            double* Gm, int64_t ldg, double* part, int ncu, double eta, double* R,
+                            int64_t ldr, double* Rdinv, int32_t* dep, int32_t* info,
+                            OrthSync* sync, double* ni_parts, hipStream_t s);
+// Q = Y R^{-1} (M x l); Y and Q may be FP32 or FP64; arithmetic in FP64.  With
+// skip_e2 (device, the e2 of OrthSync), Q = Y when it is at most 2^-60.  With
+// dep, the columns j with dep[j] != 0 are N(0, 1/M) values (Philox stream 7 under
+// `seed`, batch `call`) instead.
 hipError_t launch_trsm(bool y_f32, bool q_f32, const void* Y, int64_t ldy, int64_t M, int l,
                        int lp, const double* R, int64_t ldr, const double* Rdinv, void* Q,
-                       int64_t ldq, hipStream_t s, const double* skip_part = nullptr);
-// overwrite the columns j with dep[j] != 0 of Q (M rows) by N(0, 1/M) values
-hipError_t launch_replace(bool q_f32, void* Q, int64_t ldq, int64_t M, int l, const int32_t* dep,
-                          uint64_t seed, uint32_t call, hipStream_t s);
+                       int64_t ldq, hipStream_t s, const double* skip_e2 = nullptr,
+                       const int32_t* dep = nullptr, uint64_t seed = 0, uint32_t call = 0);
 // C = A B for upper-triangular lp x lp matrices; rows k of B with bdep[k] != 0
 // (bdep may be null) are taken as zero
 hipError_t launch_trmm_upper(const double* A, int64_t lda, const double* B, int64_t ldb,

@@ -143,7 +143,7 @@ struct OrthBufs {
   double *G = nullptr, *R1 = nullptr, *R2 = nullptr, *Rd1 = nullptr, *Rd2 = nullptr,
          *Qa = nullptr;
   int32_t *dep = nullptr, *dep2 = nullptr;
-  double* nip = nullptr;  // lp/16 parts of ||G - I||_F^2 of the second Gram matrix
+  OrthSync* sync = nullptr;
   void* part = nullptr;
   size_t part_bytes = 0;
   double* gpart = nullptr;  // partial Gram tiles, gram_part_bytes(lp, NCU_CAP)
@@ -218,7 +218,7 @@ OrthBufs take_orth(Arena& a, int64_t rows, int lp, size_t part_bytes) {
   ob.Qa = a.take<double>((size_t)rows * lp);
   ob.dep = a.take<int32_t>(lp);
   ob.dep2 = a.take<int32_t>(lp);
-  ob.nip = a.take<double>(16);
+  ob.sync = a.take<OrthSync>(8);
   ob.part_bytes = part_bytes;
   ob.part = a.take<char>(part_bytes);
   ob.gpart = a.take<double>(gram_part_bytes(lp, NCU_CAP) / sizeof(double));
@@ -310,24 +310,24 @@ hipError_t orth_p1(Ctx& c, const OrthBufs& ob, bool y_f32, const void* Y, int64_
                    int64_t rows, int l) {
   const int lp = (int)rup(l, 16);
   const int gG = std::min(c.ncu, NCU_CAP);
-  RSVD_TRY(launch_gram(y_f32, Y, ldy, rows, l, lp, ob.G, lp, ob.gpart, gG, c.st));
-  RSVD_TRY(launch_chol(ob.G, lp, l, lp, ETA_ORTH, ob.R1, lp, ob.Rd1, ob.dep, c.info, c.st));
-  RSVD_TRY(launch_trsm(y_f32, false, Y, ldy, rows, l, lp, ob.R1, lp, ob.Rd1, ob.Qa, lp, c.st));
-  return launch_replace(false, ob.Qa, lp, rows, l, ob.dep, c.seed, c.orth_calls++, c.st);
+  RSVD_TRY(launch_gram_chol(y_f32, Y, ldy, rows, l, lp, ob.G, lp, ob.gpart, gG, ETA_ORTH, ob.R1,
+                            lp, ob.Rd1, ob.dep, c.info, ob.sync, nullptr, c.st));
+  return launch_trsm(y_f32, false, Y, ldy, rows, l, lp, ob.R1, lp, ob.Rd1, ob.Qa, lp, c.st,
+                     nullptr, ob.dep, c.seed, c.orth_calls++);
 }
 
 // Second pass: Qa = Q R2.  An FP32 basis is the first pass rounded to FP32
 // when that pass is already orthonormal far below the FP32 rounding (the
-// near-identity parts decide).
+// near-identity parts decide).  (R1's inverse blocks are free by then and hold
+// the parts.)
 hipError_t orth_p2(Ctx& c, const OrthBufs& ob, int64_t rows, int l, void* Q, bool q_f32,
                    int64_t ldq) {
   const int lp = (int)rup(l, 16);
   const int gG = std::min(c.ncu, NCU_CAP);
-  RSVD_TRY(launch_gram(false, ob.Qa, lp, rows, l, lp, ob.G, lp, ob.gpart, gG, c.st));
-  RSVD_TRY(launch_chol(ob.G, lp, l, lp, ETA_ORTH, ob.R2, lp, ob.Rd2, ob.dep2, c.info, c.st,
-                       ob.nip));
+  RSVD_TRY(launch_gram_chol(false, ob.Qa, lp, rows, l, lp, ob.G, lp, ob.gpart, gG, ETA_ORTH,
+                            ob.R2, lp, ob.Rd2, ob.dep2, c.info, ob.sync, ob.Rd1, c.st));
   return launch_trsm(false, q_f32, ob.Qa, lp, rows, l, lp, ob.R2, lp, ob.Rd2, Q, ldq, c.st,
-                     q_f32 ? ob.nip : nullptr);
+                     q_f32 ? &ob.sync->e2 : nullptr);
 }
 
 // Q = orth(Y) by CholeskyQR2 (rows x l, l <= ORTH_BLOCK); optionally
@@ -473,8 +473,7 @@ hipError_t run_decompose(Ctx& c, const Shape& s, const Bufs& b, const void* A, i
   const bool f32 = s.f32;
   const int l = s.l, lp = s.lp, k = s.k;
   const int64_t m = s.m, n = s.n;
-  RSVD_TRY(launch_set_word(c.info, 0, c.st));
-  RSVD_TRY(launch_set_word(c.info + 1, 0, c.st));
+  RSVD_TRY(launch_reset(c.info, b.ob.sync, b.ob2.sync, c.st));
   // range finder
   const int at = s.atype;
   RSVD_TRY(launch_sketch(f32, c.seed, 0, 0, n, l, b.Om, lp, c.st));
@@ -598,8 +597,7 @@ hipError_t run_id_left(Ctx& c, const Shape& s, const LeftBufs& b, const void* A,
   const bool f32 = s.f32;
   const int l = s.l, lp = s.lp, k = s.k, at = s.atype;
   const int64_t m = s.m, n = s.n;
-  RSVD_TRY(launch_set_word(c.info, 0, c.st));
-  RSVD_TRY(launch_set_word(c.info + 1, 0, c.st));
+  RSVD_TRY(launch_reset(c.info, b.ob.sync, nullptr, c.st));
   RSVD_TRY(launch_sketch(f32, c.seed, STREAM_LEFT, 0, m, l, b.Ot, lp, c.st));
   RSVD_TRY(pass(c, at, true, m, n, l, A, lda, b.Ot, lp, b.Yt, lp, b.ob.part, b.ob.part_bytes,
                 b.Xt));
@@ -666,8 +664,7 @@ hipError_t run_qb(Ctx& c, const QbBufs& w, int64_t m, int64_t n, int b, int M, i
   const int bp = (int)rup(b, 16);
   const int ncu = std::min(c.ncu, NCU_CAP);
   const OrthBufs& ob = w.ob;
-  RSVD_TRY(launch_set_word(c.info, 0, c.st));
-  RSVD_TRY(launch_set_word(c.info + 1, 0, c.st));
+  RSVD_TRY(launch_reset(c.info, ob.sync, nullptr, c.st));
   int nb = 0;
   double r2 = 0.0;
   for (int i = 0; i < M; ++i) {
@@ -819,8 +816,7 @@ hipError_t run_grad(Ctx& c, const Shape& s, const GradBufs& g, const double* A, 
   const int l = s.l, lp = s.lp, k = s.k, q = s.q;
   const int64_t m = s.m, n = s.n;
   const OrthBufs& ob = g.ob;
-  RSVD_TRY(launch_set_word(c.info, 0, c.st));
-  RSVD_TRY(launch_set_word(c.info + 1, 0, c.st));
+  RSVD_TRY(launch_reset(c.info, ob.sync, nullptr, c.st));
   // forward, with the bases and factors kept
   RSVD_TRY(launch_sketch(false, c.seed, 0, 0, n, l, g.Om, lp, c.st));
   RSVD_TRY(pass(c, 0, false, m, n, l, A, lda, g.Om, lp, g.Yt, lp, ob.part, ob.part_bytes));
@@ -1477,8 +1473,7 @@ int rsvd_batch_svd(rsvd_batch_t b, uint64_t seed, const float* A, float* U, doub
   g.k0 = (uint32_t)seed; g.k1 = (uint32_t)(seed >> 32);
   g.q = b->q;
   g.info = info;
-  hipError_t e = launch_set_word(info, 0, st);
-  if (e == hipSuccess) e = launch_set_word(info + 1, 0, st);
+  hipError_t e = launch_reset(info, nullptr, nullptr, st);
   if (e == hipSuccess) e = launch_batch_rsvd(g, b->grid, st);
   return finish(e);
 }
@@ -1661,8 +1656,7 @@ int rsvd_orth(rsvd_handle_t h, int dtype, int64_t rows, int64_t l, const void* Y
   orth_step_layout(rows, (int)l, work, &ob, &Rfull);
   hipStream_t st = static_cast<hipStream_t>(stream);
   Ctx c{st, h->ncu, info, seed, 0, h};
-  hipError_t e = launch_set_word(info, 0, st);
-  if (e == hipSuccess) e = launch_set_word(info + 1, 0, st);
+  hipError_t e = launch_reset(info, ob.sync, nullptr, st);
   const bool f32 = dtype == RSVD_F32;
   if (e == hipSuccess)
     e = orth(c, ob, f32, Y, ldy, rows, (int)l, Q, f32, ldq, R ? Rfull : nullptr, lp);
@@ -1698,8 +1692,7 @@ int rsvd_small_svd(rsvd_handle_t h, int64_t l, int k, const double* Rh, int64_t 
   hipStream_t st = static_cast<hipStream_t>(stream);
   Arena a(work);
   double* jw = a.take<double>(jacobi_work_bytes((int)l) / sizeof(double) + 1);
-  hipError_t e = launch_set_word(info, 0, st);
-  if (e == hipSuccess) e = launch_set_word(info + 1, 0, st);
+  hipError_t e = launch_reset(info, nullptr, nullptr, st);
   if (e == hipSuccess)
     e = launch_jacobi(Rh, ldr, (int)l, k, jw, S, Uh, lduh, Vh, ldvh, h->jacobi_max_sweeps, info,
                       nullptr, h->giveup_test, st);
@@ -1747,8 +1740,7 @@ int rsvd_cpqr(rsvd_handle_t h, int dtype, int64_t r, int64_t c, int k, const voi
   double* S12t = a.take<double>((size_t)(c - k + 1) * kp);
   double* pv = a.take<double>(k);
   const CpqrPlan pr = plan_cpqr((int)r, c, k, std::min(h->ncu, NCU_CAP));
-  hipError_t e = launch_set_word(info, 0, st);
-  if (e == hipSuccess) e = launch_set_word(info + 1, 0, st);
+  hipError_t e = launch_reset(info, nullptr, nullptr, st);
   if (e == hipSuccess)
     e = launch_cpqr(dtype == RSVD_F32, Bcols, ldb, (int)r, c, k, pr, cw, J, S11t, S12t, kp, pv,
                     info, h->giveup_test, st);
