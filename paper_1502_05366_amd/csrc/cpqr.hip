@@ -5,7 +5,8 @@
 //
 // One launch of G <= (compute units) workgroups that wait for each other with
 // bounded spins (below); workgroup g keeps columns
-// [g*cs, (g+1)*cs) of B in LDS for the whole factorization.  Step s:
+// [g*cs, (g+1)*cs) of B for the whole factorization, in registers
+// (cpqr_reg_kernel) or, where they do not fit, in LDS (cpqr_kernel).  Step s:
 //   1. each workgroup finds its unchosen column with the largest residual
 //      norm ||B(s:, j)|| (FP64, lowest column index on ties) and publishes
 //      the norm, the index and rows s.. of that column;
@@ -17,6 +18,8 @@
 //   4. residual norms are recomputed exactly over rows s+1.. .
 // Chosen columns keep their place; the remaining columns are listed in
 // ascending index order.  The rank tolerance is max(r, c) * eps * ||B||_F.
+#include <algorithm>
+
 #include "common.h"
 #include "internal.h"
 
@@ -44,7 +47,7 @@ struct CpqrArgs {
   int32_t* info;                   // [2]
 };
 
-// Exchange between the workgroups of one step: every workgroup posts its
+// Exchange between the workgroups of one step (columns in LDS): every workgroup posts its
 // candidate into its own slot and then raises the slot's tag to step + 1
 // (release); readers wait for each tag (acquire) and read the slot with
 // agent-scope loads.  No counter is shared, so no atomic is contended.  A wait
@@ -369,6 +372,389 @@ __global__ __launch_bounds__(CQ_NT) void cpqr_kernel(CpqrArgs a) {
   }
 }
 
+// ---- columns in registers ---------------------------------------------------
+//
+// Up to 96 columns per workgroup (c <= 24576 on 256 compute units) the columns
+// stay in registers: lane rl of a row of 16 lanes holds rows rl + 16 e of its
+// NSET columns (column 32 q + 4 wave + group of the workgroup), so a step reads
+// no column from LDS and writes none.  What bounds a step is the exchange, not
+// the arithmetic (~0.5 us): three trips to memory that all compute units see.
+// The slot protocol of the kernel above takes five (data, tag, poll, candidate,
+// column), so here every 64-bit word carries 32 bits of data and the step
+// number and is its own flag: a candidate is two words, the column 32 RPL, a
+// writer waits for nothing, and one wave reads all candidates (contiguous, two
+// words per lane), picks the pivot, reads its column and forms the reflector,
+// while the others wait at a barrier (two barriers per step instead of five).
+// The arithmetic and its order are those of the kernel above.  Per step, LDS
+// kernel -> this one: 6.7 -> 4.5 us (210 x 1024), 7.1 -> 4.8 (210 x 4096), 8.7 ->
+// 6.0 (210 x 10000, two columns per lane group), 9.6 -> 6.6 (200 x 20000, three).
+// Candidates lie 128 bytes apart: eight to a line cost 0.4 - 0.9 us more, the
+// writers of one line waiting for each other.
+//
+// A word of step s is overwritten at step s + 2 (two halves), which its owner
+// reaches only after the candidates of step s + 1 of all workgroups, and those
+// follow their reads of step s.  The words are cleared before the launch.
+constexpr int CQ_MAXSET = 3;                 // 32 columns each
+constexpr int CQ_NOCAND = 0xFFFF;
+constexpr int CQ_LINE = 16;                  // words between candidates: 128 bytes
+
+__device__ __forceinline__ uint64_t ld_agent_u64(const uint64_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent_u64(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// a double as two words with a tag in their low halves
+__device__ __forceinline__ void st_tagged(uint64_t* p, double x, uint32_t tag_hi,
+                                          uint32_t tag_lo) {
+  const uint64_t b = (uint64_t)__double_as_longlong(x);
+  st_agent_u64(p, (b & 0xFFFFFFFF00000000ull) | tag_hi);
+  st_agent_u64(p + 1, (b << 32) | tag_lo);
+}
+__device__ __forceinline__ double tagged_value(uint64_t hi, uint64_t lo) {
+  return __longlong_as_double((long long)((hi & 0xFFFFFFFF00000000ull) | (lo >> 32)));
+}
+
+// (val, key) of the better candidate among the lanes that a DPP or swap
+// exchange brings together; keys rise with the column index
+__device__ __forceinline__ void keep_better(double& v, uint32_t& k, double ov, uint32_t ok) {
+  const bool b = ov > v || (ov == v && ok < k);
+  v = b ? ov : v;
+  k = b ? ok : k;
+}
+template <int CTRL> __device__ __forceinline__ void best_dpp(double& v, uint32_t& k) {
+  const double ov = dpp_d<CTRL>(v);
+  const uint32_t ok = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, CTRL, 0xF, 0xF, false);
+  keep_better(v, k, ov, ok);
+}
+// the best over the lanes i, i ^ 16 (H = 16) or i, i ^ 32 (H = 32)
+template <int H> __device__ __forceinline__ void best_swap(double& v, uint32_t& k) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  auto sw = [](uint32_t x) {
+    if constexpr (H == 16) return __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    else return __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  };
+  const auto lo = sw((uint32_t)b), hi = sw((uint32_t)(b >> 32)), kk = sw(k);
+  const double v0 = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0]));
+  const double v1 = __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+  v = v0;
+  k = kk[0];
+  keep_better(v, k, v1, kk[1]);
+}
+
+template <int RPL, int NSET>
+__global__ __launch_bounds__(CQ_NT) void cpqr_reg_kernel(CpqrArgs a, int b_f32) {
+  __shared__ double v[16 * RPL];
+  __shared__ double redf[CQ_NW];
+  __shared__ double redv[CQ_NW];
+  __shared__ uint32_t redk[CQ_NW];
+  __shared__ int32_t piv[256];
+  __shared__ double sh_beta, sh_alpha;
+  __shared__ int32_t sh_gi;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cg = lane >> 4, rl = lane & 15;
+  const int g = blockIdx.x, G = a.G;
+  const int cs = (int)a.cs, r = a.r;
+  const int64_t j0 = (int64_t)g * cs;
+  const int ncols = (int)max((int64_t)0, min(a.c - j0, (int64_t)cs));
+  uint64_t* const cand = reinterpret_cast<uint64_t*>(a.slots);       // [2][G] CQ_LINE apart
+  uint64_t* const fro = cand + (int64_t)CQ_LINE * 2 * G;                       // [G][2]
+  uint64_t* const colw = fro + (int64_t)2 * G;                       // [2][G][16 RPL][2]
+
+  double x[NSET][RPL];
+  int chosen_at[NSET];                     // step at which chosen, -1 if not, -2 no column
+  double bv = -1.0;
+  uint32_t bk = CQ_NOCAND;
+  double fpart = 0.0;
+#pragma unroll
+  for (int q = 0; q < NSET; ++q) {
+    const int jj = 32 * q + 4 * wave + cg;
+    const bool in = jj < ncols;
+    const int64_t base = (j0 + (in ? jj : 0)) * a.ldb;
+    chosen_at[q] = in ? -1 : -2;
+#pragma unroll
+    for (int e = 0; e < RPL; ++e) {
+      const int i = rl + 16 * e;
+      const int64_t off = (in && i < r) ? base + i : 0;
+      const double y = b_f32 ? (double)static_cast<const float*>(a.Bt)[off]
+                             : static_cast<const double*>(a.Bt)[off];
+      x[q][e] = (in && i < r) ? y : 0.0;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NSET; ++q) {
+    double s2 = 0.0;
+#pragma unroll
+    for (int e = 0; e < RPL; ++e) s2 = fma(x[q][e], x[q][e], s2);
+    s2 = row16_sum(s2);
+    if (chosen_at[q] == -1) {
+      if (rl == 0) {
+        fpart += s2;
+        if (!(s2 <= 1.7976931348623157e308)) info_or(a.info, INFO_NONFINITE);   // NaN or Inf in B
+      }
+      keep_better(bv, bk, sel_key(s2), (uint32_t)(32 * q + 4 * wave + cg));
+    }
+  }
+  fpart = wave_allsum(fpart);
+  if (lane == 0) redf[wave] = fpart;
+  double tol = 0.0;                        // (tol, frank and dead: wave 0)
+  int frank = a.k;
+  bool dead = false;
+
+  for (int s = 0; s < a.k; ++s) {
+    const int par = s & 1;
+    const uint32_t tag = (uint32_t)s + 1u;
+    // 1. the workgroup's candidate: the owning wave posts it and its column
+    best_swap<16>(bv, bk);
+    best_swap<32>(bv, bk);
+    if (lane == 0) { redv[wave] = bv; redk[wave] = bk; }
+    __syncthreads();
+    {
+      double cv = redv[lane & 7];
+      uint32_t ck = redk[lane & 7];
+      best_dpp<0xB1>(cv, ck);
+      best_dpp<0x4E>(cv, ck);
+      best_dpp<0x141>(cv, ck);
+      const uint32_t loc = (uint32_t)__builtin_amdgcn_readfirstlane((int)ck);
+      const int owner = loc == CQ_NOCAND ? 0 : (int)(loc >> 2) & 7;
+      if (wave == owner) {
+        if (lane == 0) st_tagged(cand + (int64_t)CQ_LINE * (par * G + g), cv, (loc << 16) | tag, tag);
+        if (loc != CQ_NOCAND) {
+          uint64_t* cw = colw + ((int64_t)par * G + g) * (32 * RPL);
+          if (cg == (int)(loc & 3)) {
+#pragma unroll
+            for (int q = 0; q < NSET; ++q)
+              if (q == (int)(loc >> 5)) {
+#pragma unroll
+                for (int e = 0; e < RPL; ++e)
+                  if (16 * e + 15 >= s) st_tagged(cw + 2 * (rl + 16 * e), x[q][e], tag, tag);
+              }
+          }
+        }
+      }
+      if (s == 0 && tid == 0) {
+        double f = 0.0;
+        for (int w = 0; w < CQ_NW; ++w) f += redf[w];
+        st_tagged(fro + 2 * g, f, tag, tag);
+      }
+    }
+    // 2. wave 0: all candidates, the pivot (largest norm, lowest index on
+    // ties), its column and the reflector
+    if (wave == 0) {
+      const uint32_t want = tag + a.wait_bias;
+      auto waits = [&](auto&& poll) {
+        for (uint32_t spins = 1; !poll() && !dead; ++spins) {
+          if ((spins & 63) == 0) {
+            if (ld_agent_u32(a.abort_flag) != 0) dead = true;
+            else if (spins > a.spin_cap) {
+              if (lane == 0) {
+                st_agent_u32(a.abort_flag, 1u);
+                info_or(a.info, INFO_BARRIER);
+              }
+              dead = true;
+            }
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+      };
+      constexpr int NQ = 4;                // G <= 256
+      // (a lane past the last workgroup holds an empty candidate)
+      uint64_t c0[NQ], c1[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const bool in = 64 * q + lane < G;
+        c0[q] = in ? 0u : ((uint32_t)CQ_NOCAND << 16) | want;
+        c1[q] = in ? 0u : want;
+      }
+      const uint64_t* cp = cand + (int64_t)CQ_LINE * par * G;
+      waits([&]() {
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          if (((uint32_t)c0[q] & 0xFFFFu) != want || (uint32_t)c1[q] != want) {
+            const int w = 64 * q + lane;
+            c0[q] = ld_agent_u64(cp + CQ_LINE * w);
+            c1[q] = ld_agent_u64(cp + CQ_LINE * w + 1);
+          }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          ok = ok && ((uint32_t)c0[q] & 0xFFFFu) == want && (uint32_t)c1[q] == want;
+        return __all(ok) != 0;
+      });
+      double gv = -1.0;
+      uint32_t gk = 0xFFFFFFFFu;           // workgroup << 16 | its column
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const uint32_t loc = (uint32_t)c0[q] >> 16;
+        const bool ok = ((uint32_t)c0[q] & 0xFFFFu) == want && (uint32_t)c1[q] == want &&
+                        loc < (uint32_t)cs;
+        if (ok)
+          keep_better(gv, gk, tagged_value(c0[q], c1[q]), ((uint32_t)(64 * q + lane) << 16) | loc);
+      }
+      best_dpp<0xB1>(gv, gk);
+      best_dpp<0x4E>(gv, gk);
+      best_dpp<0x141>(gv, gk);
+      best_dpp<0x140>(gv, gk);
+      best_swap<16>(gv, gk);
+      best_swap<32>(gv, gk);
+      gk = (uint32_t)__builtin_amdgcn_readfirstlane((int)gk);
+      gv = readlane_d(gv, 0);
+      // without a valid candidate (possible only after an aborted wait, whose
+      // results are flagged invalid) column 0 stands in, so that every index
+      // stays in range
+      int gg = (int)(gk >> 16);
+      int64_t gi = (int64_t)gg * cs + (gk & 0xFFFFu);
+      if (gk == 0xFFFFFFFFu || gi >= a.c) { gi = 0; gg = 0; }
+      constexpr int NR = (16 * RPL + 63) / 64;
+      uint64_t h[NR], o[NR];
+      const uint64_t* cw = colw + ((int64_t)par * G + gg) * (32 * RPL);
+      // (rows not posted: zero)
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const int i = 64 * q + lane;
+        h[q] = o[q] = ((i | 15) >= s && i < 16 * RPL) ? 0u : want;
+      }
+      waits([&]() {
+        bool ok = true;
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+          if ((uint32_t)h[q] != want || (uint32_t)o[q] != want) {
+            h[q] = ld_agent_u64(cw + 2 * (64 * q + lane));
+            o[q] = ld_agent_u64(cw + 2 * (64 * q + lane) + 1);
+          }
+#pragma unroll
+        for (int q = 0; q < NR; ++q) ok = ok && (uint32_t)h[q] == want && (uint32_t)o[q] == want;
+        return __all(ok) != 0;
+      });
+      if (s == 0) {
+        // the workgroups' shares of ||B||_F^2
+        double fro2 = 0.0;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          if (64 * q < G) {
+            const bool in = 64 * q + lane < G;
+            const int w = min(64 * q + lane, G - 1);
+            uint64_t f0 = 0, f1 = 0;
+            waits([&]() {
+              f0 = ld_agent_u64(fro + 2 * w);
+              f1 = ld_agent_u64(fro + 2 * w + 1);
+              return __all((uint32_t)f0 == want && (uint32_t)f1 == want) != 0;
+            });
+            fro2 += wave_allsum(in ? tagged_value(f0, f1) : 0.0);
+          }
+        tol = (double)(r > a.c ? r : a.c) * DEPS * sqrt(fro2);
+      }
+      // the pivot's posted norm^2 is ||x||^2 of its rows s..r-1; a non-finite
+      // pivot (NaN key -0.5, or Inf) is taken with a zero reflector
+      const bool pfin = gv >= 0.0 && gv <= 1.7976931348623157e308;
+      if (!pfin && g == 0 && lane == 0) info_or(a.info, INFO_NONFINITE);
+      const double normx = pfin ? sqrt(gv) : 0.0;
+      if (frank == a.k && normx <= tol) frank = s;
+      double x0 = 0.0;
+#pragma unroll
+      for (int q = 0; q < NR; ++q)
+        if (q == s >> 6) x0 = readlane_d(tagged_value(h[q], o[q]), s & 63);
+      double beta = 0.0, alpha = 0.0, v0 = x0;
+      if (normx != 0.0) {
+        const double sg = x0 >= 0.0 ? 1.0 : -1.0;
+        v0 = x0 + sg * normx;
+        alpha = -sg * normx;
+        // v^T v = 2 ||x|| (||x|| + |x_0|)
+        beta = 1.0 / (normx * (normx + fabs(x0)));
+      }
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const int i = 64 * q + lane;
+        const double y = tagged_value(h[q], o[q]);
+        if (i < 16 * RPL) v[i] = (i < s || i >= r) ? 0.0 : (i == s ? v0 : y);
+      }
+      if (lane == 0) {
+        sh_beta = beta;
+        sh_alpha = alpha;
+        sh_gi = (int32_t)gi;
+        piv[s] = (int32_t)gi;
+        if (g == 0) {
+          a.J[s] = gi;
+          a.pivn[s] = normx;
+        }
+      }
+    }
+    __syncthreads();
+    // 3. the reflector on the unchosen columns, their norms over rows s+1..
+    // and each lane's best column (rows outside s .. r-1 of v are zero)
+    const double beta = sh_beta, alpha = sh_alpha;
+    const int gl = (int)min(max((int64_t)sh_gi - j0, (int64_t)-1), (int64_t)CQ_NOCAND);
+    double vr[RPL];
+#pragma unroll
+    for (int e = 0; e < RPL; ++e) vr[e] = v[rl + 16 * e];
+    bv = -1.0;
+    bk = CQ_NOCAND;
+#pragma unroll
+    for (int q = 0; q < NSET; ++q) {
+      const int jj = 32 * q + 4 * wave + cg;
+      const bool act = chosen_at[q] == -1;
+      const bool is_piv = act && jj == gl;
+      double dp[4] = {0.0, 0.0, 0.0, 0.0};   // four partial sums: short FMA chains
+#pragma unroll
+      for (int e = 0; e < RPL; ++e) dp[e & 3] = fma(vr[e], x[q][e], dp[e & 3]);
+      const double wdot = beta * row16_sum((dp[0] + dp[1]) + (dp[2] + dp[3]));
+      const bool upd = act && !is_piv && beta != 0.0;
+#pragma unroll
+      for (int e = 0; e < RPL; ++e) {
+        const int i = rl + 16 * e;
+        const double y = fma(-wdot, vr[e], x[q][e]);
+        x[q][e] = (upd && i >= s) ? y : x[q][e];
+      }
+      if (is_piv) {
+#pragma unroll
+        for (int e = 0; e < RPL; ++e) {
+          const int i = rl + 16 * e;
+          x[q][e] = (i == s) ? alpha : (i > s ? 0.0 : x[q][e]);
+        }
+        chosen_at[q] = s;
+      }
+      double sp[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int e = 0; e < RPL; ++e) {
+        const int i = rl + 16 * e;
+        const double f = fma(x[q][e], x[q][e], sp[e & 3]);
+        sp[e & 3] = i > s ? f : sp[e & 3];
+      }
+      const double s2 = row16_sum((sp[0] + sp[1]) + (sp[2] + sp[3]));
+      if (act && !is_piv) keep_better(bv, bk, sel_key(s2), (uint32_t)jj);
+    }
+  }
+  if (g == 0 && tid == 0 && frank < a.k) {
+    info_or(a.info, INFO_RANK);
+    a.info[1] = frank;
+  }
+  // (after an aborted wait: as in the kernel above)
+  const bool dead_all = ld_agent_u32(a.abort_flag) != 0;
+  // outputs: top k rows of every owned column
+#pragma unroll
+  for (int q = 0; q < NSET; ++q) {
+    const int64_t j = j0 + 32 * q + 4 * wave + cg;
+    const int t = chosen_at[q];
+    if (t == -2) continue;
+    if (dead_all) {
+      if (rl == 0) a.J[j] = j;
+      continue;
+    }
+    int before = 0;
+    for (int i = rl; i < a.k; i += 16) before += (piv[i] < j) ? 1 : 0;
+    before += __builtin_amdgcn_update_dpp(0, before, 0xB1, 0xF, 0xF, false);
+    before += __builtin_amdgcn_update_dpp(0, before, 0x4E, 0xF, 0xF, false);
+    before += __builtin_amdgcn_update_dpp(0, before, 0x141, 0xF, 0xF, false);
+    before += __builtin_amdgcn_update_dpp(0, before, 0x140, 0xF, 0xF, false);
+    double* dst = t >= 0 ? a.S11t + (int64_t)t * a.lds : a.S12t + (j - before) * a.lds;
+    if (t < 0 && rl == 0) a.J[a.k + (j - before)] = j;
+#pragma unroll
+    for (int e = 0; e < RPL; ++e)
+      if (rl + 16 * e < a.k) dst[rl + 16 * e] = x[q][e];
+  }
+}
+
 // Upper-triangular solve X = S^{-1} B with many right-hand sides (k <= 256),
 // by block back substitution over 16 x 16 blocks:
 //   X_c = M_c (B_c - sum_{b>c} S_cb X_b),  c = nb-1 .. 0,
@@ -501,9 +887,16 @@ CpqrPlan plan_cpqr(int r, int64_t c, int k, int ncu) {
   return p;
 }
 
+// The words of the kernel with columns in registers, in 64-bit words: the abort
+// flag (the first), candidates, shares of ||B||_F^2, columns.
+static int64_t cpqr_reg_words(const CpqrPlan& p) {
+  return FLAG_STRIDE / 2 + (int64_t)p.G * (2 * CQ_LINE + 2 + 2 * 32 * p.rpl);
+}
+
 size_t cpqr_work_bytes(const CpqrPlan& p) {
-  return (size_t)(2 * p.G * p.slot_len) * sizeof(double) +
-         (size_t)(2 * p.G + 1) * FLAG_STRIDE * sizeof(uint32_t) + 64;
+  return std::max((size_t)(2 * p.G * p.slot_len) * sizeof(double) +
+                      (size_t)(2 * p.G + 1) * FLAG_STRIDE * sizeof(uint32_t),
+                  (size_t)cpqr_reg_words(p) * sizeof(uint64_t)) + 64;
 }
 
 hipError_t launch_cpqr(bool b_f32, const void* Bt, int64_t ldb, int r, int64_t c, int k,
@@ -522,10 +915,31 @@ hipError_t launch_cpqr(bool b_f32, const void* Bt, int64_t ldb, int r, int64_t c
   a.J = J; a.S11t = S11t; a.S12t = S12t; a.lds = lds; a.pivn = pivn; a.info = info;
   a.wait_bias = giveup_test ? 1u : 0u;
   a.spin_cap = giveup_test ? SPIN_CAP_TEST : SPIN_CAP;
+  const void* fn = nullptr;
+  const int nset = (int)cdiv(p.cs, 32);
+  // Three column sets of 16 rows per lane fill the 256 registers of a wave;
+  // wider B stays in LDS.
+  if (nset <= CQ_MAXSET && p.G <= 256) {
+    a.abort_flag = static_cast<uint32_t*>(work);
+    a.slots = w + FLAG_STRIDE / 2;
+    hipError_t e = launch_fill_u32(a.abort_flag, 0u, 2 * cpqr_reg_words(p), s);
+    if (e != hipSuccess) return e;
+    int f = b_f32 ? 1 : 0;
+    void* args[] = {&a, &f};
+#define RSVD_CQ1(V, N) \
+  if (p.rpl == V && nset == N) fn = (const void*)cpqr_reg_kernel<V, N>;
+#define RSVD_CQ(V) RSVD_CQ1(V, 1) RSVD_CQ1(V, 2) RSVD_CQ1(V, 3)
+    RSVD_CQ(2) RSVD_CQ(4) RSVD_CQ(8) RSVD_CQ(12) RSVD_CQ(13) RSVD_CQ(14) RSVD_CQ(16)
+#undef RSVD_CQ
+#undef RSVD_CQ1
+    if (!fn) return hipErrorInvalidValue;
+    e = hipLaunchKernel(fn, dim3(p.G), dim3(CQ_NT), args, 0, s);
+    if (e != hipSuccess) return e;
+    return hipGetLastError();
+  }
   hipError_t e = launch_fill_u32(a.tags, 0u, (2 * p.G + 1) * FLAG_STRIDE, s);
   if (e != hipSuccess) return e;
   void* args[] = {&a};
-  const void* fn = nullptr;
 #define RSVD_CQ(V)                                                                       \
   if (p.rpl == V)                                                                        \
     fn = b_f32 ? (const void*)cpqr_kernel<float, V> : (const void*)cpqr_kernel<double, V>;
