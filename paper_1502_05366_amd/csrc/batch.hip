@@ -13,9 +13,9 @@
 // the host orders the queue by decreasing work) until it is empty, so the
 // grid is one workgroup per CU whatever the batch size, and no workgroup
 // ever waits for another.  Per matrix:
-//  * passes over A (FP32 MFMA 16x16x4, FP32 accumulation): 128-row (or
-//    128-column for A^T) tiles of A and 64-deep chunks of A and the skinny
-//    operand staged in LDS with 16-byte loads, double-buffered;
+//  * passes over A (FP32 MFMA 16x16x4, FP32 accumulation): 128- or 256-row
+//    (column for A^T) tiles of A loaded straight into registers, 64- or 32-deep
+//    chunks of the skinny operand double-buffered in LDS;
 //  * orth = CholeskyQR2 in FP64: Gram X^T X on FP64 MFMA (upper blocks,
 //    rows split over the waves), Cholesky (one barrier per step) and the
 //    inverse of R (four lanes per column) in LDS, Q = Y R^{-1} on FP64 MFMA;
@@ -43,26 +43,14 @@ constexpr int BLMAX = BATCH_MAX_LP;  // lp <= 80
 constexpr int SL = BLMAX + 1;        // LDS row stride of the small FP64 matrices
 // Pass shapes (the batch autotuner picks one per matrix): a pass over A
 // takes tiles of TM = 128 RPW rows of A (A^T: columns), RPW 16-row blocks
-// per wave, and KC-deep chunks of A and of the skinny operand, double
+// per wave, and KC-deep chunks, A in registers and the skinny operand double
 // buffered in LDS.
 //   variant 0: TM = 128, KC = 64;  variant 1: TM = 256, KC = 32;
 //   variant 2: TM = 128, KC = 32.
-// LDS row strides (floats), chosen so that the operand reads of a wave hit
-// distinct banks: lane (li, lk) reads row li (stride KC + 4 = 4 or 36 mod
-// 64) at column lk of the A tile, and row lk (stride 80 = 16 mod 64, TM + 16
-// = 16 mod 64) at column li of the skinny chunk and of the A^T tile.
-template <int RPW, int KC> struct PassShape {
-  static constexpr int TM = 128 * RPW;
-  static constexpr int ALD = KC + 4;           // A tile row stride, TM x KC
-  static constexpr int ATLD = TM + 16;         // A^T tile row stride, KC x TM
-  static constexpr int STAGE_N = 2 * (TM * ALD + KC * 80);
-  static constexpr int STAGE_T = 2 * (KC * ATLD + KC * 80);
-  static constexpr int STAGE = STAGE_N > STAGE_T ? STAGE_N : STAGE_T;
-};
+// LDS row stride of the skinny chunk (floats): lane (li, lk) reads row lk at
+// column li, and 80 = 16 mod 64 puts the four rows on distinct banks.
 constexpr int XLD = 80;              // skinny chunk row stride, KC x lp
-constexpr int cmax(int a, int b) { return a > b ? a : b; }
-constexpr int STAGE_FLOATS = cmax(PassShape<1, 64>::STAGE,
-                                  cmax(PassShape<2, 32>::STAGE, PassShape<1, 32>::STAGE));
+constexpr int STAGE_FLOATS = 2 * 64 * XLD;
 constexpr double ETA_DEP = 1e-13;
 constexpr int JAC_MAX_SWEEPS = 40;
 
@@ -129,42 +117,109 @@ __device__ __noinline__ void b_sketch(float* Om, int64_t n, int l, int lp, uint3
   __syncthreads();
 }
 
-// A float4 of row r of A at column c (c % 4 == 0, c < lda), entries at
-// columns >= n taken as zero
-__device__ __forceinline__ float4 ld_a4(const float* A, int64_t lda, int64_t m, int64_t n,
-                                        int64_t r, int64_t c) {
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (r < m && c < lda) {
-    v = ld4(A + r * lda + c);
-    if (c + 0 >= n) v.x = 0.f;
-    if (c + 1 >= n) v.y = 0.f;
-    if (c + 2 >= n) v.z = 0.f;
-    if (c + 3 >= n) v.w = 0.f;
-  }
-  return v;
-}
-
 // 16-byte store (p is 16-byte aligned: every tile stride is a multiple of 4)
 __device__ __forceinline__ void st4(float* p, const float4& v) {
   *reinterpret_cast<float4*>(p) = v;
 }
 
+// Both passes keep A in registers and the skinny operand X in LDS.  Every
+// element of A is used by one wave only, so staging A in LDS (as before) bought
+// nothing but its barriers: a chunk of A had to arrive, be stored and be read
+// back while nothing else of the pass could run, and one chunk in flight per
+// compute unit (32 KB) covers a third of the memory's latency.  Here a wave
+// loads the A of its own rows (columns for A^T) straight into the layout of the
+// products, two chunks ahead, each register replaced as soon as it is consumed;
+// X chunks are double buffered in LDS with one barrier per chunk that waits for
+// LDS only, so loads of A stay in flight across it.
+//
+// Order of the FP32 sums: k ascending in steps of 4.  4096 matrices of up to 2048
+// x 1024, k <= 64, one power step: 44.2 -> 36.8 ms for the whole batch (the passes
+// 22 -> 15 of it).
+
+// X chunk kc (KC rows x lp; rows >= n are zero) through registers to LDS
+template <int NCB, int KC> struct XChunk {
+  static constexpr int lp = 16 * NCB, XQ = lp / 4, XN = KC * XQ;
+  static constexpr int F4 = (XN + BNT - 1) / BNT;
+  float4 v[F4];
+  bool in[F4];
+  __device__ __forceinline__ void load(const float* X, int64_t n, int64_t kc) {
+    const bool past = kc * KC >= n;
+    const int64_t r0 = past ? 0 : kc * KC;
+#pragma unroll
+    for (int u = 0; u < F4; ++u) {
+      const int idx = min((int)threadIdx.x + BNT * u, XN - 1);
+      // clamped and selected: no branch waits for the load
+      const int left = (int)min(n - r0, (int64_t)KC);
+      const int r = idx / XQ;
+      v[u] = ld4(X + r0 * lp + min(r, left - 1) * lp + (idx % XQ) * 4);
+      in[u] = r < left && !past;
+    }
+  }
+  __device__ __forceinline__ void store(float* xs) const {
+#pragma unroll
+    for (int u = 0; u < F4; ++u) {
+      const int idx = threadIdx.x + BNT * u;
+      const float4 z = in[u] ? v[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+      if (idx < XN) st4(xs + (idx / XQ) * XLD + (idx % XQ) * 4, z);
+    }
+  }
+};
+
+// The arguments of a function that is not inlined arrive in vector registers;
+// these are the same in every lane.
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <typename T> __device__ __forceinline__ T* uniform(T* p) {
+  return reinterpret_cast<T*>(uniform((int64_t)reinterpret_cast<intptr_t>(p)));
+}
+
+// LDS stores of this wave done, then the workgroup's barrier (outstanding loads
+// from memory are not waited for)
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// x[c] of lane group g = value (g, c)  ->  x[t] of lane group g = value (t, g)
+// (lane groups of 16; a 4 x 4 transposition over the groups)
+__device__ __forceinline__ void transpose_groups(float (&x)[4]) {
+  auto sw32 = [](float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  };
+  auto sw16 = [](float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+  };
+  sw32(x[0], x[2]);
+  sw32(x[1], x[3]);
+  sw16(x[0], x[1]);
+  sw16(x[2], x[3]);
+}
+
 // Y (m x lp) = A X, A m x n (FP32, lda % 4 == 0), X n x lp (FP32), lp = 16 NCB.
-// Row tiles of TM (16 RPW rows per wave), KC-deep chunks of A and X in LDS.
+// Row tiles of TM (16 RPW rows per wave), KC-deep chunks.  A lane loads 4
+// consecutive k of its row (16 bytes); transpose_groups brings them into the
+// order of the products.
 template <int NCB, int RPW, int KC>
 __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, int64_t m,
                                       int64_t n, const float* __restrict__ X,
                                       float* __restrict__ Y) {
-  using S = PassShape<RPW, KC>;
-  constexpr int lp = 16 * NCB, TM = S::TM, ALD = S::ALD;
-  constexpr int AF4 = TM * KC / 4 / BNT;             // float4 of the A tile per thread
-  constexpr int KQ = KC / 4;                          // float4 per A tile row
-  constexpr int XF4 = (KC * 20 + BNT - 1) / BNT;      // float4 of the X chunk per thread (lp <= 80)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int lp = 16 * NCB, TM = 128 * RPW, NG = KC / 16;
+  A = uniform(A); X = uniform(X); Y = uniform(Y);
+  lda = uniform(lda); m = uniform(m); n = uniform(n);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  float* st = g_lds.u.stage;
-  const int xq = lp / 4;                                // float4 per X row
-  const int xn = KC * xq;                               // float4 per X chunk
+  float* const xs0 = g_lds.u.stage;
   const int64_t nkc = cdiv(n, KC);
   for (int64_t row0 = 0; row0 < m; row0 += TM) {
     f4 acc[RPW][NCB];
@@ -172,62 +227,67 @@ __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, 
     for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = f4{0.f, 0.f, 0.f, 0.f};
-    float4 av[AF4], xv[XF4];
-    auto gload = [&](int64_t kc) {
-      const int64_t k0 = kc * KC;
+    const float* ar[RPW];
 #pragma unroll
-      for (int u = 0; u < AF4; ++u) {
-        const int idx = tid + BNT * u;
-        av[u] = ld_a4(A, lda, m, n, row0 + idx / KQ, k0 + (idx % KQ) * 4);
-      }
+    for (int rb = 0; rb < RPW; ++rb)
+      ar[rb] = A + min(row0 + (wave * RPW + rb) * 16 + li, m - 1) * lda;
+    float4 a[2][NG][RPW];
+    // group j of chunk kc: columns kc KC + 16 j + 4 lk .. + 3 of the lane's rows
+    auto aload = [&](float4 (&d)[RPW], int64_t kc, int j) {
+      const int64_t c = min(kc * KC + 16 * j, lda - 4);
+      const int e = min(4 * lk, (int)min(lda - 4 - c, (int64_t)12));
 #pragma unroll
-      for (int u = 0; u < XF4; ++u) {
-        const int idx = tid + BNT * u;
-        const int xr = idx / xq, xc = (idx - (idx / xq) * xq) * 4;
-        xv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (idx < xn && k0 + xr < n) xv[u] = ld4(X + (k0 + xr) * lp + xc);
-      }
+      for (int rb = 0; rb < RPW; ++rb) d[rb] = ld4(ar[rb] + c + e);
     };
-    auto sstore = [&](int b) {
-      float* as = st + b * (TM * ALD);
-      float* xs = st + 2 * TM * ALD + b * (KC * XLD);
+    XChunk<NCB, KC> x;
+    x.load(X, n, 0);
 #pragma unroll
-      for (int u = 0; u < AF4; ++u) {
-        const int idx = tid + BNT * u;
-        st4(as + (idx / KQ) * ALD + (idx % KQ) * 4, av[u]);
-      }
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int u = 0; u < XF4; ++u) {
-        const int idx = tid + BNT * u;
-        if (idx < xn) {
-          const int xr = idx / xq, xc = (idx - (idx / xq) * xq) * 4;
-          st4(xs + xr * XLD + xc, xv[u]);
-        }
-      }
-    };
-    gload(0);
-    sstore(0);
-    __syncthreads();
-    for (int64_t kc = 0; kc < nkc; ++kc) {
-      const bool more = kc + 1 < nkc;
-      if (more) gload(kc + 1);
-      const float* as = st + (kc & 1) * (TM * ALD);
-      const float* xs = st + 2 * TM * ALD + (kc & 1) * (KC * XLD);
+      for (int j = 0; j < NG; ++j) aload(a[h][j], h, j);
+    x.store(xs0);
+    x.load(X, n, 1);
+    lds_barrier();
+    auto chunk = [&](int h, int64_t kc) {
+      const float* xs = xs0 + h * (KC * XLD);
+      x.store(xs0 + (h ^ 1) * (KC * XLD));     // chunk kc + 1 (read from the barrier on)
+      x.load(X, n, kc + 2);
 #pragma unroll
-      for (int kk = 0; kk < KC / 4; ++kk) {
+      for (int j = 0; j < NG; ++j) {
+        float y[RPW][4];
 #pragma unroll
         for (int rb = 0; rb < RPW; ++rb) {
-          const float a = as[((wave * RPW + rb) * 16 + li) * ALD + kk * 4 + lk];
+          const float4 v = a[h][j][rb];
+          y[rb][0] = v.x; y[rb][1] = v.y; y[rb][2] = v.z; y[rb][3] = v.w;
+          if (kc * KC + 16 * j + 16 > n) {     // entries at columns >= n count as zero
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb)
-            acc[rb][cb] =
-                Mfma<float>::mma(a, xs[(kk * 4 + lk) * XLD + cb * 16 + li], acc[rb][cb]);
+            for (int c = 0; c < 4; ++c)
+              y[rb][c] = kc * KC + 16 * j + 4 * lk + c < n ? y[rb][c] : 0.f;
+          }
+          transpose_groups(y[rb]);
         }
-        if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        aload(a[h][j], kc + 2, j);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          float xv[NCB];
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) xv[cb] = xs[(16 * j + 4 * t + lk) * XLD + cb * 16 + li];
+#pragma unroll
+          for (int rb = 0; rb < RPW; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb)
+              acc[rb][cb] = Mfma<float>::mma(y[rb][t], xv[cb], acc[rb][cb]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      if (more) sstore((kc + 1) & 1);
-      __syncthreads();
+      lds_barrier();
+    };
+    int64_t kc = 0;
+    for (; kc + 1 < nkc; kc += 2) {
+      chunk(0, kc);
+      chunk(1, kc + 1);
     }
+    if (kc < nkc) chunk(0, kc);
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
@@ -243,92 +303,93 @@ __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, 
 }
 
 // Z (n x lp) = A^T X, A m x n (FP32, lda % 4 == 0), X m x lp (FP32), lp = 16 NCB.
-// Tiles of TM columns of A (16 RPW per wave), KC-row chunks of A and X in LDS.
+// Tiles of TM columns of A, 16 RPW per wave (block rb of a wave holds every
+// RPW-th of them, so a lane loads RPW neighbours), KC-row chunks.
 template <int NCB, int RPW, int KC>
 __device__ __noinline__ void b_pass_t(const float* __restrict__ A, int64_t lda, int64_t m,
                                       int64_t n, const float* __restrict__ X,
                                       float* __restrict__ Z) {
-  using S = PassShape<RPW, KC>;
-  constexpr int lp = 16 * NCB, TM = S::TM, ATLD = S::ATLD;
-  constexpr int AF4 = TM * KC / 4 / BNT;
-  constexpr int TQ = TM / 4;                          // float4 per A tile row
-  constexpr int XF4 = (KC * 20 + BNT - 1) / BNT;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int lp = 16 * NCB, TM = 128 * RPW, NS = KC / 4;
+  A = uniform(A); X = uniform(X); Z = uniform(Z);
+  lda = uniform(lda); m = uniform(m); n = uniform(n);
+  static_assert(RPW <= 2, "");
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
-  float* st = g_lds.u.stage;
-  const int xq = lp / 4;
-  const int xn = KC * xq;
+  float* const xs0 = g_lds.u.stage;
   const int64_t nkc = cdiv(m, KC);
+  const int64_t last = (m - 1) & ~(int64_t)3;            // first row of the last 4-row step
+  const int tail = (int)(m - 1 - last);
   for (int64_t col0 = 0; col0 < n; col0 += TM) {
     f4 acc[RPW][NCB];
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) acc[rb][cb] = f4{0.f, 0.f, 0.f, 0.f};
-    float4 av[AF4], xv[XF4];
-    auto gload = [&](int64_t kc) {
-      const int64_t r0 = kc * KC;
-#pragma unroll
-      for (int u = 0; u < AF4; ++u) {
-        const int idx = tid + BNT * u;
-        av[u] = ld_a4(A, lda, m, n, r0 + idx / TQ, col0 + (idx % TQ) * 4);
-      }
-#pragma unroll
-      for (int u = 0; u < XF4; ++u) {
-        const int idx = tid + BNT * u;
-        const int xr = idx / xq, xc = (idx - (idx / xq) * xq) * 4;
-        xv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (idx < xn && r0 + xr < m) xv[u] = ld4(X + (r0 + xr) * lp + xc);
+    // the lane's columns (past the last ones: loaded, not stored)
+    const int64_t c0 = min(col0 + (wave * 16 + li) * RPW, lda - RPW);
+    const float* const al = A + lk * lda + c0;                     // row lk of a step
+    const float* const at = A + min(lk, tail) * lda + c0;          // ... of the last step
+    float a[2][NS][RPW];
+    auto aload = [&](float (&d)[RPW], int64_t kc, int j) {
+      const int64_t r = min(kc * KC + 4 * j, last);
+      const float* p = (r == last ? at : al) + r * lda;
+      if constexpr (RPW == 2) {
+        const float2 v = *reinterpret_cast<const float2*>(p);
+        d[0] = v.x;
+        d[1] = v.y;
+      } else {
+        d[0] = *p;
       }
     };
-    auto sstore = [&](int b) {
-      float* as = st + b * (KC * ATLD);
-      float* xs = st + 2 * KC * ATLD + b * (KC * XLD);
+    XChunk<NCB, KC> x;
+    x.load(X, m, 0);
 #pragma unroll
-      for (int u = 0; u < AF4; ++u) {
-        const int idx = tid + BNT * u;
-        st4(as + (idx / TQ) * ATLD + (idx % TQ) * 4, av[u]);
-      }
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int u = 0; u < XF4; ++u) {
-        const int idx = tid + BNT * u;
-        if (idx < xn) {
-          const int xr = idx / xq, xc = (idx - (idx / xq) * xq) * 4;
-          st4(xs + xr * XLD + xc, xv[u]);
+      for (int j = 0; j < NS; ++j) aload(a[h][j], h, j);
+    x.store(xs0);
+    x.load(X, m, 1);
+    lds_barrier();
+    auto chunk = [&](int h, int64_t kc) {
+      const float* xs = xs0 + h * (KC * XLD);
+      x.store(xs0 + (h ^ 1) * (KC * XLD));
+      x.load(X, m, kc + 2);
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        float y[RPW];
+#pragma unroll
+        for (int rb = 0; rb < RPW; ++rb) y[rb] = a[h][j][rb];
+        if (kc * KC + 4 * j + 4 > m) {         // rows >= m count as zero
+#pragma unroll
+          for (int rb = 0; rb < RPW; ++rb) y[rb] = kc * KC + 4 * j + lk < m ? y[rb] : 0.f;
         }
-      }
-    };
-    gload(0);
-    sstore(0);
-    __syncthreads();
-    for (int64_t kc = 0; kc < nkc; ++kc) {
-      const bool more = kc + 1 < nkc;
-      if (more) gload(kc + 1);
-      const float* as = st + (kc & 1) * (KC * ATLD);
-      const float* xs = st + 2 * KC * ATLD + (kc & 1) * (KC * XLD);
+        float xv[NCB];
 #pragma unroll
-      for (int kk = 0; kk < KC / 4; ++kk) {
+        for (int cb = 0; cb < NCB; ++cb) xv[cb] = xs[(4 * j + lk) * XLD + cb * 16 + li];
 #pragma unroll
-        for (int rb = 0; rb < RPW; ++rb) {
-          // A^T[col][row]: column (wave RPW + rb) 16 + li of the tile, row kk*4 + lk
-          const float a = as[(kk * 4 + lk) * ATLD + (wave * RPW + rb) * 16 + li];
+        for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb)
-            acc[rb][cb] =
-                Mfma<float>::mma(a, xs[(kk * 4 + lk) * XLD + cb * 16 + li], acc[rb][cb]);
-        }
-        if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            acc[rb][cb] = Mfma<float>::mma(y[rb], xv[cb], acc[rb][cb]);
+        aload(a[h][j], kc + 2, j);
+        if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
-      if (more) sstore((kc + 1) & 1);
-      __syncthreads();
+      lds_barrier();
+    };
+    int64_t kc = 0;
+    for (; kc + 1 < nkc; kc += 2) {
+      chunk(0, kc);
+      chunk(1, kc + 1);
     }
+    if (kc < nkc) chunk(0, kc);
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int64_t c = col0 + (wave * RPW + rb) * 16 + Mfma<float>::row(lk, v);
+          const int64_t c = col0 + (wave * 16 + Mfma<float>::row(lk, v)) * RPW + rb;
           if (c < n) Z[c * lp + cb * 16 + li] = acc[rb][cb][v];
         }
       }
