@@ -1,5 +1,4 @@
-// Batched randomized SVD of many small FP32 matrices in one persistent
-// launch: Alg. 5 (RSVD version II) with re-orthonormalization after every
+// Batched randomized SVD of many small FP32 matrices in persistent launches: Alg. 5 (RSVD version II) with re-orthonormalization after every
 // product (Sec. 3.2, s = 1), applied to each matrix of the batch on its own.
 // The matrices are independent, as the blocks of Alg. 8 are, so each one is
 // the work of a single workgroup:
@@ -11,8 +10,8 @@
 //
 // A workgroup of 8 waves pops matrices off a work queue (an atomic counter;
 // the host orders the queue by decreasing work) until it is empty, so the
-// grid is one workgroup per CU whatever the batch size, and no workgroup
-// ever waits for another.  Per matrix:
+// grid is one workgroup per CU (two where l <= 64) whatever the batch size, and
+// no workgroup ever waits for another.  Per matrix:
 //  * passes over A (FP32 MFMA 16x16x4, FP32 accumulation): 128- or 256-row
 //    (column for A^T) tiles of A loaded straight into registers, 64- or 32-deep
 //    chunks of the skinny operand double-buffered in LDS;
@@ -39,8 +38,6 @@ namespace rsvd {
 namespace {
 
 constexpr int BNT = 512;             // 8 waves
-constexpr int BLMAX = BATCH_MAX_LP;  // lp <= 80
-constexpr int SL = BLMAX + 1;        // LDS row stride of the small FP64 matrices
 // Pass shapes (the batch autotuner picks one per matrix): a pass over A
 // takes tiles of TM = 128 RPW rows of A (A^T: columns), RPW 16-row blocks
 // per wave, and KC-deep chunks, A in registers and the skinny operand double
@@ -54,28 +51,38 @@ constexpr int STAGE_FLOATS = 2 * 64 * XLD;
 constexpr double ETA_DEP = 1e-13;
 constexpr int JAC_MAX_SWEEPS = 40;
 
-// LDS of a workgroup: the passes stage their tiles over the whole union; the
-// small factorizations use a, b (lp x lp FP64, stride SL) and the Gram
-// partials.  Declared at namespace scope so that every helper addresses it
-// as LDS even when it is not inlined.
-struct alignas(16) BatchLds {
+// LDS of a workgroup: the passes stage the skinny operand over the whole union;
+// the small factorizations use a, b (lp x lp FP64, stride SL).  Declared at
+// namespace scope so that every helper addresses it as LDS even when it is not
+// inlined.  Two layouts, ML = 64 and 80 (the largest lp that fits): 68 KB lets two
+// workgroups share a compute unit, 105 KB does not.
+template <int ML> struct alignas(16) BatchLds {
+  static constexpr int SL = ML + 1;              // row stride of the small FP64 matrices
   union {
     struct {
-      double a[BLMAX * SL];
-      double b[BLMAX * SL];
-      double part[8 * 256];
+      double a[ML * SL];
+      double b[ML * SL];
     } sm;
     float stage[STAGE_FLOATS];
   } u;
-  double sig[BLMAX];
-  double dgn[BLMAX];
-  int depc[BLMAX];     // columns found dependent by the last Cholesky
+  double sig[ML];
+  double dgn[ML];
+  int depc[ML];        // columns found dependent by the last Cholesky
   int ndep;            // how many
   int nonfinite;       // a non-finite pivot was met (this matrix)
   int flag;
   int item;
 };
-__shared__ BatchLds g_lds;
+__shared__ BatchLds<BATCH_SMALL_LP> g_lds_small;
+__shared__ BatchLds<BATCH_MAX_LP> g_lds_large;
+template <int ML> __device__ __forceinline__ BatchLds<ML>& batch_lds() {
+  if constexpr (ML == BATCH_SMALL_LP) return g_lds_small;
+  else return g_lds_large;
+}
+// the LDS layout of a matrix with lp = 16 NB
+template <int NB> constexpr int ml_of() {
+  return 16 * NB <= BATCH_SMALL_LP ? BATCH_SMALL_LP : BATCH_MAX_LP;
+}
 
 __device__ __forceinline__ double to_d(float x) { return (double)x; }
 __device__ __forceinline__ double to_d(double x) { return x; }
@@ -83,12 +90,24 @@ template <typename T> __device__ __forceinline__ T from_d(double x);
 template <> __device__ __forceinline__ float from_d<float>(double x) { return (float)x; }
 template <> __device__ __forceinline__ double from_d<double>(double x) { return x; }
 
+// The arguments of a function that is not inlined arrive in vector registers;
+// these are the same in every lane.
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <typename T> __device__ __forceinline__ T* uniform(T* p) {
+  return reinterpret_cast<T*>(uniform((int64_t)reinterpret_cast<intptr_t>(p)));
+}
+
 __device__ __forceinline__ float4 ld4(const float* p) {
   return *reinterpret_cast<const float4*>(p);
 }
 
 // Omega (n x lp, FP32): column j < l holds normals j*n .. j*n + n-1 of stream
 // 0, batch `batch`; columns l .. lp-1 are zero.
+template <int ML>   // (a copy per kernel: they differ in registers)
 __device__ __noinline__ void b_sketch(float* Om, int64_t n, int l, int lp, uint32_t k0,
                                       uint32_t k1, uint32_t batch) {
   const int tid = threadIdx.x;
@@ -133,8 +152,10 @@ __device__ __forceinline__ void st4(float* p, const float4& v) {
 // LDS only, so loads of A stay in flight across it.
 //
 // Order of the FP32 sums: k ascending in steps of 4.  4096 matrices of up to 2048
-// x 1024, k <= 64, one power step: 44.2 -> 36.8 ms for the whole batch (the passes
-// 22 -> 15 of it).
+// x 1024, k <= 64, one power step, the whole batch: 44.2 -> 36.8 ms.
+// Chunks of A in flight per wave: with two workgroups on a compute unit one
+// chunk each (and half the registers), otherwise two.
+template <int NCB> constexpr int pass_ahead() { return 16 * NCB <= BATCH_SMALL_LP ? 1 : 2; }
 
 // X chunk kc (KC rows x lp; rows >= n are zero) through registers to LDS
 template <int NCB, int KC> struct XChunk {
@@ -164,17 +185,6 @@ template <int NCB, int KC> struct XChunk {
     }
   }
 };
-
-// The arguments of a function that is not inlined arrive in vector registers;
-// these are the same in every lane.
-__device__ __forceinline__ int64_t uniform(int64_t x) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-template <typename T> __device__ __forceinline__ T* uniform(T* p) {
-  return reinterpret_cast<T*>(uniform((int64_t)reinterpret_cast<intptr_t>(p)));
-}
 
 // LDS stores of this wave done, then the workgroup's barrier (outstanding loads
 // from memory are not waited for)
@@ -213,6 +223,9 @@ template <int NCB, int RPW, int KC>
 __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, int64_t m,
                                       int64_t n, const float* __restrict__ X,
                                       float* __restrict__ Y) {
+  auto& g_lds = batch_lds<ml_of<NCB>()>();
+  constexpr int SL = BatchLds<ml_of<NCB>()>::SL;
+  (void)SL;
   constexpr int lp = 16 * NCB, TM = 128 * RPW, NG = KC / 16;
   A = uniform(A); X = uniform(X); Y = uniform(Y);
   lda = uniform(lda); m = uniform(m); n = uniform(n);
@@ -231,7 +244,8 @@ __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, 
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb)
       ar[rb] = A + min(row0 + (wave * RPW + rb) * 16 + li, m - 1) * lda;
-    float4 a[2][NG][RPW];
+    constexpr int D = pass_ahead<NCB>();
+    float4 a[D][NG][RPW];
     // group j of chunk kc: columns kc KC + 16 j + 4 lk .. + 3 of the lane's rows
     auto aload = [&](float4 (&d)[RPW], int64_t kc, int j) {
       const int64_t c = min(kc * KC + 16 * j, lda - 4);
@@ -242,15 +256,16 @@ __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, 
     XChunk<NCB, KC> x;
     x.load(X, n, 0);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < D; ++h)
 #pragma unroll
       for (int j = 0; j < NG; ++j) aload(a[h][j], h, j);
     x.store(xs0);
     x.load(X, n, 1);
     lds_barrier();
-    auto chunk = [&](int h, int64_t kc) {
-      const float* xs = xs0 + h * (KC * XLD);
-      x.store(xs0 + (h ^ 1) * (KC * XLD));     // chunk kc + 1 (read from the barrier on)
+    auto chunk = [&](int h, int64_t kc) {      // h = kc mod D
+      const int xb = (int)(kc & 1);
+      const float* xs = xs0 + xb * (KC * XLD);
+      x.store(xs0 + (xb ^ 1) * (KC * XLD));     // chunk kc + 1 (read from the barrier on)
       x.load(X, n, kc + 2);
 #pragma unroll
       for (int j = 0; j < NG; ++j) {
@@ -266,7 +281,7 @@ __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, 
           }
           transpose_groups(y[rb]);
         }
-        aload(a[h][j], kc + 2, j);
+        aload(a[h][j], kc + D, j);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           float xv[NCB];
@@ -283,11 +298,15 @@ __device__ __noinline__ void b_pass_n(const float* __restrict__ A, int64_t lda, 
       lds_barrier();
     };
     int64_t kc = 0;
-    for (; kc + 1 < nkc; kc += 2) {
-      chunk(0, kc);
-      chunk(1, kc + 1);
+    if constexpr (D == 2) {
+      for (; kc + 1 < nkc; kc += 2) {
+        chunk(0, kc);
+        chunk(1, kc + 1);
+      }
+      if (kc < nkc) chunk(0, kc);
+    } else {
+      for (; kc < nkc; ++kc) chunk(0, kc);
     }
-    if (kc < nkc) chunk(0, kc);
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
@@ -309,6 +328,9 @@ template <int NCB, int RPW, int KC>
 __device__ __noinline__ void b_pass_t(const float* __restrict__ A, int64_t lda, int64_t m,
                                       int64_t n, const float* __restrict__ X,
                                       float* __restrict__ Z) {
+  auto& g_lds = batch_lds<ml_of<NCB>()>();
+  constexpr int SL = BatchLds<ml_of<NCB>()>::SL;
+  (void)SL;
   constexpr int lp = 16 * NCB, TM = 128 * RPW, NS = KC / 4;
   A = uniform(A); X = uniform(X); Z = uniform(Z);
   lda = uniform(lda); m = uniform(m); n = uniform(n);
@@ -330,7 +352,8 @@ __device__ __noinline__ void b_pass_t(const float* __restrict__ A, int64_t lda, 
     const int64_t c0 = min(col0 + (wave * 16 + li) * RPW, lda - RPW);
     const float* const al = A + lk * lda + c0;                     // row lk of a step
     const float* const at = A + min(lk, tail) * lda + c0;          // ... of the last step
-    float a[2][NS][RPW];
+    constexpr int D = pass_ahead<NCB>();
+    float a[D][NS][RPW];
     auto aload = [&](float (&d)[RPW], int64_t kc, int j) {
       const int64_t r = min(kc * KC + 4 * j, last);
       const float* p = (r == last ? at : al) + r * lda;
@@ -345,15 +368,16 @@ __device__ __noinline__ void b_pass_t(const float* __restrict__ A, int64_t lda, 
     XChunk<NCB, KC> x;
     x.load(X, m, 0);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < D; ++h)
 #pragma unroll
       for (int j = 0; j < NS; ++j) aload(a[h][j], h, j);
     x.store(xs0);
     x.load(X, m, 1);
     lds_barrier();
-    auto chunk = [&](int h, int64_t kc) {
-      const float* xs = xs0 + h * (KC * XLD);
-      x.store(xs0 + (h ^ 1) * (KC * XLD));
+    auto chunk = [&](int h, int64_t kc) {      // h = kc mod D
+      const int xb = (int)(kc & 1);
+      const float* xs = xs0 + xb * (KC * XLD);
+      x.store(xs0 + (xb ^ 1) * (KC * XLD));
       x.load(X, m, kc + 2);
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
@@ -372,17 +396,21 @@ __device__ __noinline__ void b_pass_t(const float* __restrict__ A, int64_t lda, 
 #pragma unroll
           for (int cb = 0; cb < NCB; ++cb)
             acc[rb][cb] = Mfma<float>::mma(y[rb], xv[cb], acc[rb][cb]);
-        aload(a[h][j], kc + 2, j);
+        aload(a[h][j], kc + D, j);
         if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
       lds_barrier();
     };
     int64_t kc = 0;
-    for (; kc + 1 < nkc; kc += 2) {
-      chunk(0, kc);
-      chunk(1, kc + 1);
+    if constexpr (D == 2) {
+      for (; kc + 1 < nkc; kc += 2) {
+        chunk(0, kc);
+        chunk(1, kc + 1);
+      }
+      if (kc < nkc) chunk(0, kc);
+    } else {
+      for (; kc < nkc; ++kc) chunk(0, kc);
     }
-    if (kc < nkc) chunk(0, kc);
 #pragma unroll
     for (int rb = 0; rb < RPW; ++rb)
 #pragma unroll
@@ -401,9 +429,13 @@ __device__ __noinline__ void b_pass_t(const float* __restrict__ A, int64_t lda, 
 // MFMA.  Tasks (16x16 block, row slice) are spread over the 8 waves; with
 // fewer than 8 blocks the rows are cut into slices whose partial blocks are
 // added in slice order.  Eight 4-row steps are loaded before their products.
-template <typename TX, typename TY>
+template <int ML, typename TX, typename TY>
 __device__ __noinline__ void b_xty(const TX* __restrict__ X, const TY* __restrict__ Y,
                                    int64_t rows, int lp) {
+  auto& g_lds = batch_lds<ML>();
+  constexpr int SL = BatchLds<ML>::SL;
+  (void)SL;
+  X = uniform(X); Y = uniform(Y); rows = uniform(rows);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const int nb = lp / 16, nblk = nb * nb;
@@ -411,7 +443,7 @@ __device__ __noinline__ void b_xty(const TX* __restrict__ X, const TY* __restric
   const int ntask = nblk * S;
   const int64_t nsteps = cdiv(rows, 4);
   double* out = g_lds.u.sm.a;
-  double* part = g_lds.u.sm.part;
+  double* part = out + 32 * SL;     // (sliced only with at most two column blocks)
   for (int task = wave; task < ntask; task += 8) {
     const int b = task / S, sl = task - (task / S) * S;
     const int bi = b / nb, bj = b - (b / nb) * nb;
@@ -421,13 +453,16 @@ __device__ __noinline__ void b_xty(const TX* __restrict__ X, const TY* __restric
       double av[8], bv[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int64_t r = (st + u) * 4 + lk;
-        const bool ok = st + u < st1 && r < rows;
-        av[u] = ok ? to_d(X[r * lp + bi * 16 + li]) : 0.0;
-        bv[u] = ok ? to_d(Y[r * lp + bj * 16 + li]) : 0.0;
+        // (clamped, not branched around)
+        const int64_t r = min((st + u) * 4 + lk, rows - 1) * lp;
+        av[u] = to_d(X[r + bi * 16 + li]);
+        bv[u] = to_d(Y[r + bj * 16 + li]);
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc = Mfma<double>::mma(av[u], bv[u], acc);
+      for (int u = 0; u < 8; ++u) {
+        const bool ok = st + u < st1 && (st + u) * 4 + lk < rows;
+        acc = Mfma<double>::mma(ok ? av[u] : 0.0, ok ? bv[u] : 0.0, acc);
+      }
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -451,13 +486,16 @@ __device__ __noinline__ void b_xty(const TX* __restrict__ X, const TY* __restric
 }
 
 // a (upper 16x16 blocks, stride SL) = X^T X for X rows x lp (FP32 or FP64)
-// on FP64 MFMA.  Wave w forms every upper block over its eighth of the rows
-// (two 4-row steps loaded before their products); the eight partial Grams
-// are added into a in wave order.
+// on FP64 MFMA.  Wave w forms every upper block over its eighth of the rows; the eight partial Grams are added into a in wave order.
 template <int NB, typename TX>
 __device__ __noinline__ void b_gram(const TX* __restrict__ X, int64_t rows) {
+  auto& g_lds = batch_lds<ml_of<NB>()>();
+  constexpr int SL = BatchLds<ml_of<NB>()>::SL;
+  (void)SL;
   constexpr int lp = 16 * NB, nb = NB;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  X = uniform(X); rows = uniform(rows);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   double* out = g_lds.u.sm.a;
   const int64_t nsteps = cdiv(rows, 4);
@@ -467,22 +505,44 @@ __device__ __noinline__ void b_gram(const TX* __restrict__ X, int64_t rows) {
   for (int bi = 0; bi < NB; ++bi)
 #pragma unroll
     for (int bj = bi; bj < NB; ++bj) acc[bi][bj] = d4{0.0, 0.0, 0.0, 0.0};
-  for (int64_t st = st0; st < st1; st += 2) {
-    double xv[2][NB];
+  // U steps at a time, the next U in flight meanwhile (the registers: 128 up to
+  // NB = 4); addresses are clamped and steps outside the wave's eighth or past
+  // the last row count as zero, so no branch waits for a load
+  constexpr int U = NB <= 2 ? 4 : (NB == 4 && sizeof(TX) == 8 ? 1 : 2);
+  const int64_t last = (rows - 1) / 4;
+  const int off = lk * lp + li, off_last = min(lk, (int)(rows - 1 - 4 * last)) * lp + li;
+  TX x0[U][NB], x1[U][NB];
+  auto load = [&](TX (&x)[U][NB], int64_t st) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int64_t r = (st + u) * 4 + lk;
-      const bool ok = st + u < st1 && r < rows;
+    for (int u = 0; u < U; ++u) {
+      const int64_t t = min(st + u, last);
+      const TX* p = X + t * (4 * lp);
+      const int o = t == last ? off_last : off;
 #pragma unroll
-      for (int bi = 0; bi < NB; ++bi) xv[u][bi] = ok ? to_d(X[r * lp + bi * 16 + li]) : 0.0;
+      for (int bi = 0; bi < NB; ++bi) x[u][bi] = p[o + bi * 16];
     }
+  };
+  auto products = [&](const TX (&x)[U][NB], int64_t st) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < U; ++u) {
+      const bool ok = st + u < st1 && (st + u) * 4 + lk < rows;
+      double xv[NB];
+#pragma unroll
+      for (int bi = 0; bi < NB; ++bi) xv[bi] = ok ? to_d(x[u][bi]) : 0.0;
 #pragma unroll
       for (int bi = 0; bi < NB; ++bi)
 #pragma unroll
         for (int bj = bi; bj < NB; ++bj)
-          acc[bi][bj] = Mfma<double>::mma(xv[u][bi], xv[u][bj], acc[bi][bj]);
+          acc[bi][bj] = Mfma<double>::mma(xv[bi], xv[bj], acc[bi][bj]);
+    }
+  };
+  load(x0, st0);
+#pragma unroll 1
+  for (int64_t st = st0; st < st1; st += 2 * U) {
+    load(x1, st + U);
+    products(x0, st);
+    load(x0, st + 2 * U);
+    products(x1, st + U);
   }
   for (int w = 0; w < 8; ++w) {
     if (wave == w) {
@@ -506,7 +566,11 @@ __device__ __noinline__ void b_gram(const TX* __restrict__ X, int64_t rows) {
 // pivot <= ETA_DEP * G_jj (or not positive) gives a unit row and sets the
 // flag.  Step j reads only row j of G and updates rows > j, so one barrier
 // per step suffices.
+template <int ML>
 __device__ __noinline__ void b_chol(int l, int lp) {
+  auto& g_lds = batch_lds<ML>();
+  constexpr int SL = BatchLds<ML>::SL;
+  (void)SL;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double* G = g_lds.u.sm.a;
   double* R = g_lds.u.sm.b;
@@ -545,7 +609,11 @@ __device__ __noinline__ void b_chol(int l, int lp) {
 // a = R^{-1} with R = b (upper triangular, lp x lp): four lanes per column c
 // solve R x = e_c by back substitution, each summing a quarter of every dot
 // product; rows / columns l .. lp-1 are the identity.
+template <int ML>
 __device__ __noinline__ void b_rinv(int l, int lp) {
+  auto& g_lds = batch_lds<ML>();
+  constexpr int SL = BatchLds<ML>::SL;
+  (void)SL;
   const int tid = threadIdx.x;
   const double* R = g_lds.u.sm.b;
   double* X = g_lds.u.sm.a;
@@ -581,17 +649,20 @@ __device__ __noinline__ void b_rinv(int l, int lp) {
 template <int NB, typename TI, typename TO>
 __device__ __noinline__ void b_apply(const TI* __restrict__ In, int64_t rows, int ncols,
                                      TO* __restrict__ Out, int64_t ldo) {
+  auto& g_lds = batch_lds<ml_of<NB>()>();
+  constexpr int SL = BatchLds<ml_of<NB>()>::SL;
+  (void)SL;
   constexpr int lp = 16 * NB;
+  In = uniform(In); Out = uniform(Out); rows = uniform(rows); ldo = uniform(ldo);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
   const double* B = g_lds.u.sm.a;
   const int64_t nrb = cdiv(rows, 16);
   for (int64_t rb = wave; rb < nrb; rb += 8) {
-    const int64_t r = rb * 16 + li;
-    const bool ok = r < rows;
+    const int64_t r = min(rb * 16 + li, rows - 1);   // (rows past the last: not stored)
     double av[4 * NB];
 #pragma unroll
-    for (int t = 0; t < 4 * NB; ++t) av[t] = ok ? to_d(In[r * lp + 4 * t + lk]) : 0.0;
+    for (int t = 0; t < 4 * NB; ++t) av[t] = to_d(In[r * lp + 4 * t + lk]);
     d4 acc[NB];
 #pragma unroll
     for (int cb = 0; cb < NB; ++cb) acc[cb] = d4{0.0, 0.0, 0.0, 0.0};
@@ -622,7 +693,11 @@ __device__ __noinline__ void b_apply(const TI* __restrict__ In, int64_t rows, in
 // ||G - I||_F^2 of the leading l x l block of the Gram in a (upper blocks:
 // diagonal terms once, off-diagonal ones twice), the same value on every
 // thread
+template <int ML>
 __device__ double b_gram_offset2(int l) {
+  auto& g_lds = batch_lds<ML>();
+  constexpr int SL = BatchLds<ML>::SL;
+  (void)SL;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* G = g_lds.u.sm.a;
   double t = 0.0;
@@ -646,10 +721,19 @@ __device__ double b_gram_offset2(int l) {
   return r;
 }
 
-// Q = T rounded to TO (rows x lp)
+// Q = T rounded to TO (rows x lp; lp is a multiple of 16, both 256-byte aligned)
 template <typename TO>
 __device__ void b_copy(const double* T, int64_t rows, int lp, TO* Q) {
-  for (int64_t e = threadIdx.x; e < rows * lp; e += BNT) Q[e] = from_d<TO>(T[e]);
+  struct alignas(4 * sizeof(TO)) Vec { TO v[4]; };
+  struct alignas(32) DVec { double v[4]; };
+#pragma unroll 4
+  for (int64_t e = threadIdx.x; e < rows * lp / 4; e += BNT) {
+    const DVec x = reinterpret_cast<const DVec*>(T)[e];
+    Vec y;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) y.v[i] = from_d<TO>(x.v[i]);
+    reinterpret_cast<Vec*>(Q)[e] = y;
+  }
   __syncthreads();
 }
 
@@ -661,8 +745,12 @@ constexpr double ORTH_SKIP2 = 0x1.0p-60;   // (2^-30)^2
 // The columns of T (rows x lp) found dependent by the first Cholesky get
 // N(0, 1/rows) entries: normal number j*rows + i of Philox stream 7 with
 // batch word (orth call << 20 | matrix index), under the call's seed.
+template <int ML>
 __device__ __noinline__ void b_replace(double* T, int64_t rows, int l, int lp, uint32_t k0,
                                        uint32_t k1, uint32_t word) {
+  auto& g_lds = batch_lds<ML>();
+  constexpr int SL = BatchLds<ML>::SL;
+  (void)SL;
   const double scale = 1.0 / sqrt((double)rows);
   for (int j = 0; j < l; ++j) {
     if (!g_lds.depc[j]) continue;
@@ -690,19 +778,22 @@ __device__ __noinline__ void b_replace(double* T, int64_t rows, int l, int lp, u
 template <int NB, typename TI, typename TO>
 __device__ void b_orth(const TI* In, int64_t rows, int l, double* T, TO* Q, uint32_t k0,
                        uint32_t k1, uint32_t word) {
-  constexpr int lp = 16 * NB;
+  auto& g_lds = batch_lds<ml_of<NB>()>();
+  constexpr int SL = BatchLds<ml_of<NB>()>::SL;
+  (void)SL;
+  constexpr int lp = 16 * NB, ML = ml_of<NB>();
   b_gram<NB>(In, rows);
-  b_chol(l, lp);
-  b_rinv(l, lp);
+  b_chol<ML>(l, lp);
+  b_rinv<ML>(l, lp);
   b_apply<NB>(In, rows, lp, T, (int64_t)lp);
-  if (g_lds.ndep > 0) b_replace(T, rows, l, lp, k0, k1, word);
+  if (g_lds.ndep > 0) b_replace<ML>(T, rows, l, lp, k0, k1, word);
   b_gram<NB>(T, rows);
-  if (b_gram_offset2(l) <= ORTH_SKIP2) {
+  if (b_gram_offset2<ML>(l) <= ORTH_SKIP2) {
     b_copy(T, rows, lp, Q);
     return;
   }
-  b_chol(l, lp);
-  b_rinv(l, lp);
+  b_chol<ML>(l, lp);
+  b_rinv<ML>(l, lp);
   b_apply<NB>(T, rows, lp, Q, (int64_t)lp);
 }
 
@@ -714,6 +805,9 @@ __device__ void b_orth(const TI* In, int64_t rows, int l, double* T, TO* Q, uint
 template <int NB>
 __device__ __noinline__ void b_jacobi(int l, int k, double* S, double* Uh, double* Vh, int lp,
                                       int32_t* info) {
+  auto& g_lds = batch_lds<ml_of<NB>()>();
+  constexpr int SL = BatchLds<ml_of<NB>()>::SL;
+  (void)SL;
   const int tid = threadIdx.x;
   const int grp = tid >> 4, li = tid & 15;
   double* W = g_lds.u.sm.b;
@@ -755,7 +849,11 @@ __device__ __noinline__ void b_jacobi(int l, int k, double* S, double* Uh, doubl
 }
 
 // a (stride SL, lp x lp) = the l x k matrix M (ld lp, global), zero elsewhere
+template <int ML>
 __device__ void b_load_small(const double* M, int l, int k, int lp) {
+  auto& g_lds = batch_lds<ML>();
+  constexpr int SL = BatchLds<ML>::SL;
+  (void)SL;
   double* B = g_lds.u.sm.a;
   const int nc = lp;
   for (int e = threadIdx.x; e < lp * nc; e += BNT) {
@@ -771,7 +869,10 @@ __device__ __noinline__ void b_one(const BatchArgs& g, const BatchDesc& d, const
                                    const float* Om,
                       float* Y, float* Q, float* Z, float* Zq, double* T, double* Qh,
                       double* Uh, double* Vh) {
-  constexpr int lp = 16 * NB;
+  auto& g_lds = batch_lds<ml_of<NB>()>();
+  constexpr int SL = BatchLds<ml_of<NB>()>::SL;
+  (void)SL;
+  constexpr int lp = 16 * NB, ML = ml_of<NB>();
   const int64_t m = d.m, n = d.n;
   const int l = d.l, k = d.k;
   // batch word of the replacement columns: orth call (high bits), matrix
@@ -787,17 +888,18 @@ __device__ __noinline__ void b_one(const BatchArgs& g, const BatchDesc& d, const
   b_orth<NB>(Y, m, l, T, Q, g.k0, g.k1, (call++ << 20) | mw);
   b_pass_t<NB, RPW, KC>(A, d.lda, m, n, Q, Z);   // B^T
   b_orth<NB>(Z, n, l, T, Qh, g.k0, g.k1, (call++ << 20) | mw);
-  b_xty(Qh, Z, n, lp);                         // Rh = Qh^T B^T
+  b_xty<ML>(Qh, Z, n, lp);                         // Rh = Qh^T B^T
   if (threadIdx.x == 0 && g_lds.flag) info_or(g.info, INFO_ORTH_FALLBACK);
   if (threadIdx.x == 0 && g_lds.nonfinite) info_or(g.info, INFO_NONFINITE);
   b_jacobi<NB>(l, k, g.S + d.s_off, Uh, Vh, lp, g.info);
-  b_load_small(Vh, l, k, lp);
+  b_load_small<ML>(Vh, l, k, lp);
   b_apply<NB>(Q, m, k, g.U + d.u_off, (int64_t)k);
-  b_load_small(Uh, l, k, lp);
+  b_load_small<ML>(Uh, l, k, lp);
   b_apply<NB>(Qh, n, k, g.V + d.v_off, (int64_t)k);
 }
 
-__global__ __launch_bounds__(BNT) void batch_rsvd_kernel(BatchArgs g) {
+template <int ML> __device__ __forceinline__ void batch_rsvd(const BatchArgs& g) {
+  auto& g_lds = batch_lds<ML>();
   const int tid = threadIdx.x;
   char* slot = g.scratch + (int64_t)blockIdx.x * g.slot_bytes;
   float* Om = reinterpret_cast<float*>(slot + g.off_om);
@@ -823,7 +925,7 @@ __global__ __launch_bounds__(BNT) void batch_rsvd_kernel(BatchArgs g) {
       g_lds.nonfinite = 0;
     }
     __syncthreads();
-    b_sketch(Om, d.n, d.l, lp, g.k0, g.k1, (uint32_t)d.index);
+    b_sketch<ML>(Om, d.n, d.l, lp, g.k0, g.k1, (uint32_t)d.index);
     // (lp / 16, pass shape) -> one instantiation
 #define RSVD_B1(NBV)                                                                     \
   switch (d.variant) {                                                                   \
@@ -831,24 +933,42 @@ __global__ __launch_bounds__(BNT) void batch_rsvd_kernel(BatchArgs g) {
     case 2: b_one<NBV, 1, 32>(g, d, A, Om, Y, Q, Z, Zq, T, Qh, Uh, Vh); break;           \
     default: b_one<NBV, 1, 64>(g, d, A, Om, Y, Q, Z, Zq, T, Qh, Uh, Vh); break;          \
   }
-    switch (lp / 16) {
-      case 1: RSVD_B1(1); break;
-      case 2: RSVD_B1(2); break;
-      case 3: RSVD_B1(3); break;
-      case 4: RSVD_B1(4); break;
-      default: RSVD_B1(5); break;
+    if constexpr (ML == BATCH_SMALL_LP) {
+      switch (lp / 16) {
+        case 1: RSVD_B1(1); break;
+        case 2: RSVD_B1(2); break;
+        case 3: RSVD_B1(3); break;
+        default: RSVD_B1(4); break;
+      }
+    } else {
+      RSVD_B1(5);
     }
 #undef RSVD_B1
   }
 }
 
+// Half of a matrix's time goes to phases of one workgroup's latency (Cholesky,
+// inverse, Jacobi) in which a compute unit's matrix cores and memory wait: with
+// two workgroups on it the phases of two matrices overlap (the batch above: 36.8
+// -> 32.0 ms, and 29.3 ms with the loads of the FP64 steps in flight across their
+// products).
+__global__ __launch_bounds__(BNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+batch_small_kernel(BatchArgs g) {
+  batch_rsvd<BATCH_SMALL_LP>(g);
+}
+__global__ __launch_bounds__(BNT) void batch_large_kernel(BatchArgs g) {
+  batch_rsvd<BATCH_MAX_LP>(g);
+}
+
 }  // namespace
 
-hipError_t launch_batch_rsvd(const BatchArgs& g, int grid, hipStream_t st) {
-  if (grid < 1 || g.count < 1) return hipErrorInvalidValue;
+hipError_t launch_batch_rsvd(const BatchArgs& g, int grid, bool small, hipStream_t st) {
+  if (g.count < 1) return hipSuccess;
+  if (grid < 1) return hipErrorInvalidValue;
   hipError_t e = launch_set_word(g.counter, 0, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(batch_rsvd_kernel, dim3((unsigned)grid), dim3(BNT), 0, st, g);
+  if (small) hipLaunchKernelGGL(batch_small_kernel, dim3((unsigned)grid), dim3(BNT), 0, st, g);
+  else hipLaunchKernelGGL(batch_large_kernel, dim3((unsigned)grid), dim3(BNT), 0, st, g);
   return hipGetLastError();
 }
 

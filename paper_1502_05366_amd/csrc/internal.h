@@ -219,8 +219,10 @@ hipError_t launch_add(double* X, int64_t ldx, const double* Y, int64_t ldy, int6
 
 // ----------------------------------------------------------------- batch --
 // Batched randomized SVD of small FP32 matrices, one workgroup per matrix in
-// one persistent launch.
+// persistent launches: one for lp <= 64, two workgroups per compute unit, one for
+// lp = 80, one per compute unit.
 constexpr int BATCH_MAX_LP = 80;     // l = min(k + p, m, n) <= 80
+constexpr int BATCH_SMALL_LP = 64;
 constexpr int BATCH_VARIANTS = 3;    // pass shapes of the batch kernel
 struct BatchDesc {
   int64_t m, n, lda;                 // A_i: m x n row-major, lda % 4 == 0
@@ -243,7 +245,7 @@ struct BatchArgs {
   int q;
   int32_t* info;
 };
-hipError_t launch_batch_rsvd(const BatchArgs& g, int grid, hipStream_t st);
+hipError_t launch_batch_rsvd(const BatchArgs& g, int grid, bool small, hipStream_t st);
 
 // ------------------------------------------------------------------- cur --
 // atype: element type of A, 0 FP64, 1 FP32, 2 BF16

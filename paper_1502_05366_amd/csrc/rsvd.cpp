@@ -46,14 +46,18 @@ struct rsvd_batch_s {
   rsvd_handle_s* h;
   int64_t count;
   int p, q;
-  std::vector<rsvd::BatchDesc> desc;     // queue order (decreasing work)
+  std::vector<rsvd::BatchDesc> desc;     // queue order (by part, decreasing work)
   std::vector<int64_t> a_off, lda, u_off, s_off, v_off;   // caller order
   int64_t a_elems, u_elems, s_elems, v_elems;
-  int64_t mmax, nmax;
-  int grid;
-  // workspace layout
-  int64_t desc_off, slot_off, slot_bytes;
-  int64_t off_om, off_y, off_q, off_z, off_zq, off_t, off_qh, off_uh, off_vh;
+  // The two launches: 0 the matrices with lp = 80, 1 those with lp <= 64, each
+  // with its part of the descriptors and its slots (one per workgroup).
+  struct Part {
+    int64_t first, count;
+    int grid;
+    int64_t slot_off, slot_bytes;
+    int64_t off_om, off_y, off_q, off_z, off_zq, off_t, off_qh, off_uh, off_vh;
+  } part[2];
+  int64_t desc_off;
   size_t work_bytes;
   const void* prepared;                  // the workspace that holds the descriptors
 };
@@ -1340,7 +1344,6 @@ int rsvd_batch_create(rsvd_handle_t h, int64_t count, const int64_t* m, const in
   b->a_off.resize(count); b->lda.resize(count); b->u_off.resize(count);
   b->s_off.resize(count); b->v_off.resize(count);
   int64_t ao = 0, uo = 0, so = 0, vo = 0;
-  b->mmax = b->nmax = 0;
   std::vector<BatchDesc> d(count);
   for (int64_t i = 0; i < count; ++i) {
     const int64_t ld = rup(n[i], 4);
@@ -1358,37 +1361,51 @@ int rsvd_batch_create(rsvd_handle_t h, int64_t count, const int64_t* m, const in
     uo += m[i] * k[i];
     so += k[i];
     vo += n[i] * k[i];
-    b->mmax = std::max(b->mmax, m[i]);
-    b->nmax = std::max(b->nmax, n[i]);
   }
   b->a_elems = ao; b->u_elems = uo; b->s_elems = so; b->v_elems = vo;
-  // queue order: decreasing work (passes 2 (2q+2) m n l), ties by index
+  // queue order: lp = 80 first, then decreasing work (passes 2 (2q+2) m n l),
+  // ties by index
+  auto part_of = [&](int64_t x) { return d[x].lp > BATCH_SMALL_LP ? 0 : 1; };
   std::vector<int64_t> ord(count);
   std::iota(ord.begin(), ord.end(), 0);
   std::stable_sort(ord.begin(), ord.end(), [&](int64_t x, int64_t y) {
+    if (part_of(x) != part_of(y)) return part_of(x) < part_of(y);
     return d[x].m * d[x].n * d[x].l > d[y].m * d[y].n * d[y].l;
   });
   b->desc.resize(count);
   for (int64_t i = 0; i < count; ++i) b->desc[i] = d[ord[i]];
-  b->grid = (int)std::min<int64_t>(h->ncu, count);
-  // workspace: [queue head][descriptors][one slot per workgroup]
-  const int64_t lpm = BATCH_MAX_LP;
-  const int64_t rmax = std::max(b->mmax, b->nmax);
+  // workspace: [queue heads][descriptors][one slot per workgroup]
   auto r256 = [](int64_t x) { return (x + 255) & ~(int64_t)255; };
-  int64_t o = 0;
-  b->off_om = o; o = r256(o + b->nmax * lpm * 4);
-  b->off_y = o;  o = r256(o + b->mmax * lpm * 4);
-  b->off_q = o;  o = r256(o + b->mmax * lpm * 4);
-  b->off_z = o;  o = r256(o + b->nmax * lpm * 4);
-  b->off_zq = o; o = r256(o + b->nmax * lpm * 4);
-  b->off_t = o;  o = r256(o + rmax * lpm * 8);
-  b->off_qh = o; o = r256(o + b->nmax * lpm * 8);
-  b->off_uh = o; o = r256(o + lpm * lpm * 8);
-  b->off_vh = o; o = r256(o + lpm * lpm * 8);
-  b->slot_bytes = o;
   b->desc_off = 256;
-  b->slot_off = r256(b->desc_off + count * (int64_t)sizeof(BatchDesc));
-  b->work_bytes = (size_t)(b->slot_off + b->grid * b->slot_bytes);
+  int64_t end = r256(b->desc_off + count * (int64_t)sizeof(BatchDesc));
+  int64_t first = 0;
+  for (int t = 0; t < 2; ++t) {
+    rsvd_batch_s::Part& pt = b->part[t];
+    pt.first = first;
+    int64_t mmax = 0, nmax = 0, lpm = 0;
+    for (; first < count && (b->desc[first].lp > BATCH_SMALL_LP ? 0 : 1) == t; ++first) {
+      mmax = std::max(mmax, b->desc[first].m);
+      nmax = std::max(nmax, b->desc[first].n);
+      lpm = std::max<int64_t>(lpm, b->desc[first].lp);
+    }
+    pt.count = first - pt.first;
+    pt.grid = (int)std::min<int64_t>((t + 1) * (int64_t)h->ncu, pt.count);
+    const int64_t rmax = std::max(mmax, nmax);
+    int64_t o = 0;
+    pt.off_om = o; o = r256(o + nmax * lpm * 4);
+    pt.off_y = o;  o = r256(o + mmax * lpm * 4);
+    pt.off_q = o;  o = r256(o + mmax * lpm * 4);
+    pt.off_z = o;  o = r256(o + nmax * lpm * 4);
+    pt.off_zq = o; o = r256(o + nmax * lpm * 4);
+    pt.off_t = o;  o = r256(o + rmax * lpm * 8);
+    pt.off_qh = o; o = r256(o + nmax * lpm * 8);
+    pt.off_uh = o; o = r256(o + lpm * lpm * 8);
+    pt.off_vh = o; o = r256(o + lpm * lpm * 8);
+    pt.slot_bytes = o;
+    pt.slot_off = end;
+    end += pt.grid * pt.slot_bytes;
+  }
+  b->work_bytes = (size_t)end;
   b->prepared = nullptr;
   *plan = b;
   return RSVD_OK;
@@ -1460,21 +1477,24 @@ int rsvd_batch_svd(rsvd_batch_t b, uint64_t seed, const float* A, float* U, doub
   if (hipSetDevice(b->h->device) != hipSuccess) return RSVD_ERR_HIP;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(work);
-  BatchArgs g;
-  g.desc = reinterpret_cast<const BatchDesc*>(w + b->desc_off);
-  g.count = b->count;
-  g.counter = reinterpret_cast<int32_t*>(w);
-  g.A = A; g.U = U; g.S = S; g.V = V;
-  g.scratch = w + b->slot_off;
-  g.slot_bytes = b->slot_bytes;
-  g.off_om = b->off_om; g.off_y = b->off_y; g.off_q = b->off_q; g.off_z = b->off_z;
-  g.off_zq = b->off_zq; g.off_t = b->off_t; g.off_qh = b->off_qh; g.off_uh = b->off_uh;
-  g.off_vh = b->off_vh;
-  g.k0 = (uint32_t)seed; g.k1 = (uint32_t)(seed >> 32);
-  g.q = b->q;
-  g.info = info;
   hipError_t e = launch_reset(info, nullptr, nullptr, st);
-  if (e == hipSuccess) e = launch_batch_rsvd(g, b->grid, st);
+  for (int t = 0; t < 2 && e == hipSuccess; ++t) {
+    const rsvd_batch_s::Part& pt = b->part[t];
+    BatchArgs g;
+    g.desc = reinterpret_cast<const BatchDesc*>(w + b->desc_off) + pt.first;
+    g.count = pt.count;
+    g.counter = reinterpret_cast<int32_t*>(w) + t;
+    g.A = A; g.U = U; g.S = S; g.V = V;
+    g.scratch = w + pt.slot_off;
+    g.slot_bytes = pt.slot_bytes;
+    g.off_om = pt.off_om; g.off_y = pt.off_y; g.off_q = pt.off_q; g.off_z = pt.off_z;
+    g.off_zq = pt.off_zq; g.off_t = pt.off_t; g.off_qh = pt.off_qh; g.off_uh = pt.off_uh;
+    g.off_vh = pt.off_vh;
+    g.k0 = (uint32_t)seed; g.k1 = (uint32_t)(seed >> 32);
+    g.q = b->q;
+    g.info = info;
+    e = launch_batch_rsvd(g, pt.grid, t == 1, st);
+  }
   return finish(e);
 }
 
