@@ -277,8 +277,8 @@ int rsvd_svd_grad(rsvd_handle_t h, int dtype, int64_t m, int64_t n, int k, int p
  * rsvd_batch_prepare: copies the plan's descriptor table into the workspace
  *   (rsvd_batch_workspace_bytes bytes, 256-byte aligned) and synchronizes the
  *   stream; once per workspace, outside any stream capture.
- * rsvd_batch_svd: launches only kernels (a queue reset and the persistent
- *   kernel), so it may be captured into a graph and replayed; calls that
+ * rsvd_batch_svd: launches only kernels (queue resets and the persistent
+ *   kernels), so it may be captured into a graph and replayed; calls that
  *   share a workspace must not overlap.  `work` must be the workspace last
  *   passed to rsvd_batch_prepare for this plan (-7 otherwise).  info (2
  *   int32, device) as for the other calls. */

@@ -60,6 +60,10 @@ struct rsvd_batch_s {
   int64_t desc_off;
   size_t work_bytes;
   const void* prepared;                  // the workspace that holds the descriptors
+  // the second launch's stream and the events that fork and join it (created by
+  // the first prepare of a plan with both parts)
+  hipStream_t aux = nullptr;
+  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
 };
 
 // Scratch of rsvd_svd_noalloc: a fixed array in device memory, one copy per
@@ -1412,6 +1416,12 @@ int rsvd_batch_create(rsvd_handle_t h, int64_t count, const int64_t* m, const in
 }
 
 int rsvd_batch_destroy(rsvd_batch_t plan) {
+  if (plan) {
+    // (their work is ordered before a join; both are released when it is done)
+    if (plan->aux) (void)hipStreamDestroy(plan->aux);
+    if (plan->ev_fork) (void)hipEventDestroy(plan->ev_fork);
+    if (plan->ev_join) (void)hipEventDestroy(plan->ev_join);
+  }
   delete plan;
   return RSVD_OK;
 }
@@ -1458,6 +1468,13 @@ int rsvd_batch_prepare(rsvd_batch_t b, void* work, size_t work_bytes, void* stre
                      hipMemcpyHostToDevice, st) != hipSuccess)
     return RSVD_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return RSVD_ERR_HIP;
+  if (b->part[0].count > 0 && b->part[1].count > 0 && !b->aux) {
+    if (!b->ev_fork && hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming) != hipSuccess)
+      return RSVD_ERR_HIP;
+    if (!b->ev_join && hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming) != hipSuccess)
+      return RSVD_ERR_HIP;
+    if (hipStreamCreateWithFlags(&b->aux, hipStreamNonBlocking) != hipSuccess) return RSVD_ERR_HIP;
+  }
   b->prepared = work;
   return RSVD_OK;
 }
@@ -1478,8 +1495,18 @@ int rsvd_batch_svd(rsvd_batch_t b, uint64_t seed, const float* A, float* U, doub
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* w = static_cast<char*>(work);
   hipError_t e = launch_reset(info, nullptr, nullptr, st);
+  // The parts side by side: the workgroups of the second fill the compute units
+  // as those of the first run out of matrices (one after the other the last,
+  // uneven matrices of the first hold up the second: 29.3 -> 26.9 ms for 4096
+  // matrices, one in eight of them in the first part).
+  const bool fork = b->part[0].count > 0 && b->part[1].count > 0;
+  if (e == hipSuccess && fork) {
+    e = hipEventRecord(b->ev_fork, st);
+    if (e == hipSuccess) e = hipStreamWaitEvent(b->aux, b->ev_fork, 0);
+  }
   for (int t = 0; t < 2 && e == hipSuccess; ++t) {
     const rsvd_batch_s::Part& pt = b->part[t];
+    const hipStream_t ts = fork && t == 1 ? b->aux : st;
     BatchArgs g;
     g.desc = reinterpret_cast<const BatchDesc*>(w + b->desc_off) + pt.first;
     g.count = pt.count;
@@ -1493,7 +1520,11 @@ int rsvd_batch_svd(rsvd_batch_t b, uint64_t seed, const float* A, float* U, doub
     g.k0 = (uint32_t)seed; g.k1 = (uint32_t)(seed >> 32);
     g.q = b->q;
     g.info = info;
-    e = launch_batch_rsvd(g, pt.grid, t == 1, st);
+    e = launch_batch_rsvd(g, pt.grid, t == 1, ts);
+  }
+  if (fork && e == hipSuccess) {
+    e = hipEventRecord(b->ev_join, b->aux);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, b->ev_join, 0);
   }
   return finish(e);
 }
