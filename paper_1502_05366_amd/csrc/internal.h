@@ -130,14 +130,18 @@ hipError_t launch_zero_dep_rows(double* R, int64_t ldr, int l, int lp, const int
 // ---------------------------------------------------------------- jacobi --
 // work: jacobi_work_bytes(l) bytes; sweeps_out (device int, may be null)
 // receives the number of sweeps of the block iteration.  The block iteration
-// (l > 64) waits across at most 8 workgroups of one ordinary launch (bounded
-// spins, INFO_BARRIER on give-up): the caller keeps that many CUs free of
-// other waiting kernels.  giveup_test: every cross-workgroup wait waits for a
+// (l > 64) waits across the workgroups of one ordinary launch (bounded spins,
+// INFO_BARRIER on give-up): without an exchange area at most 8 for l <= 256, and
+// the caller keeps that many CUs free of other waiting kernels; with one (xch,
+// jacobi_exchange_bytes(l) bytes, unused by others until the iteration ends) up to
+// 144 small ones.  giveup_test: every cross-workgroup wait waits for a
 // value no workgroup posts, with a small spin cap (failure-handling tests).
 size_t jacobi_work_bytes(int l);
+size_t jacobi_exchange_bytes(int l);
 hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* work, double* S,
                          double* Uh, int64_t lduh, double* Vh, int64_t ldvh, int max_sweeps,
-                         int32_t* info, int32_t* sweeps_out, bool giveup_test, hipStream_t s);
+                         int32_t* info, int32_t* sweeps_out, bool giveup_test, hipStream_t s,
+                         double* xch, size_t xch_bytes, int ncu);
 
 // ------------------------------------------------------------------ cpqr --
 struct CpqrPlan {

@@ -221,6 +221,101 @@ __device__ __forceinline__ void pair_cols(bool inner, int t, int P, int& p, int&
   }
 }
 
+// Whether a pair of the block pair passes the rotation test on the fresh G
+// (element e = i BS + j of the first BS^2 threads).
+__device__ __forceinline__ int jac_any_pair(const double* G, int e, bool inner, double tol) {
+  const double tol2 = tol * tol;
+  const int i = e / BS, j = e % BS;
+  const double gc = G[i * GLD + BS + j];
+  int need = gc * gc > tol2 * (G[i * GLD + i] * G[(BS + j) * GLD + BS + j]);
+  if (inner && i < j) {
+    const double gx = G[i * GLD + j], gy = G[(BS + i) * GLD + BS + j];
+    need |= gx * gx > tol2 * (G[i * GLD + i] * G[j * GLD + j]);
+    need |= gy * gy > tol2 * (G[(BS + i) * GLD + BS + i] * G[(BS + j) * GLD + BS + j]);
+  }
+  return need;
+}
+
+// LDS stores done, then the workgroup's barrier (loads from memory stay in flight)
+__device__ __forceinline__ void jac_lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// The steps of a round on G and J (every thread of the workgroup calls it).
+// Thread (I, K) of the first BS^2 (I = tid / BS, K = lane % BS) owns the 2 x 2
+// blocks of G and of J on the rows of pair I and the columns of pair K (the pairs
+// of a step partition the 2BS columns, so the blocks partition G and J).  Every
+// lane computes the rotation of its pair K and takes that of pair I from a lane of
+// its own row of 16 whose K is I, so one barrier per step suffices: G is read from
+// one copy and written to the other, each J block is read and written by its owner
+// only.
+// A round in which no pair of the block pair passes the rotation test
+// on the fresh G rotates nothing (G never changes), so its steps are
+// skipped: the same decisions as running them.  Every sweep's last
+// round set is such a check.
+__device__ __forceinline__ void jac_steps(double* G, double* Jm, const int* ptab, int tid,
+                                          int lane, int ninner, double tol, int& rotated,
+                                          int& rround) {
+  const int I = tid / BS, K = tid % BS;
+  const int srcI = (lane & ~(BS - 1)) | I;
+  // one step on the pairs (pI, qI) of thread row I and (pK, qK) of
+  // thread column K, G read from copy st & 1
+  auto step = [&](int st, int pI, int qI, int pK, int qK) {
+    const double* Gc = G + (st & 1) * JJ * GLD;
+    double* Gn = G + ((st + 1) & 1) * JJ * GLD;
+    const double aK = Gc[pK * GLD + pK], bK = Gc[qK * GLD + qK], gK = Gc[pK * GLD + qK];
+    const double gpp = Gc[pI * GLD + pK], gpq = Gc[pI * GLD + qK];
+    const double gqp = Gc[qI * GLD + pK], gqq = Gc[qI * GLD + qK];
+    const double jpp = Jm[pI * GLD + pK], jpq = Jm[pI * GLD + qK];
+    const double jqp = Jm[qI * GLD + pK], jqq = Jm[qI * GLD + qK];
+    double cK = 1.0, sK = 0.0, tK = 0.0;
+    const bool rK = jacobi_rotation_t(aK, bK, gK, tol, cK, sK, tK);
+    if (!rK) { cK = 1.0; sK = 0.0; }
+    // (1, 0) for a pair that does not turn: the products below are then
+    // exact copies
+    const double cI = __shfl(cK, srcI, 64), sI = __shfl(sK, srcI, 64);
+    if (I == K) {
+      if (rK) { rotated = 1; rround = 1; }
+      Gn[pK * GLD + pK] = rK ? aK - tK * gK : aK;
+      Gn[qK * GLD + qK] = rK ? bK + tK * gK : bK;
+      Gn[pK * GLD + qK] = rK ? 0.0 : gK;
+      Gn[qK * GLD + pK] = rK ? 0.0 : gK;
+    } else {
+      // rows by the rotation of pair I, then columns by that of pair K
+      const double rpp = cI * gpp - sI * gqp, rqp = sI * gpp + cI * gqp;
+      const double rpq = cI * gpq - sI * gqq, rqq = sI * gpq + cI * gqq;
+      Gn[pI * GLD + pK] = cK * rpp - sK * rpq;
+      Gn[pI * GLD + qK] = sK * rpp + cK * rpq;
+      Gn[qI * GLD + pK] = cK * rqp - sK * rqq;
+      Gn[qI * GLD + qK] = sK * rqp + cK * rqq;
+    }
+    // J <- J J_t on the block: its columns pK, qK turn by pair K
+    if (rK) {
+      Jm[pI * GLD + pK] = cK * jpp - sK * jpq;
+      Jm[pI * GLD + qK] = sK * jpp + cK * jpq;
+      Jm[qI * GLD + pK] = cK * jqp - sK * jqq;
+      Jm[qI * GLD + qK] = sK * jqp + cK * jqq;
+    }
+  };
+#pragma unroll 1
+  for (int st = 0; st < ninner + BS; ++st) {
+    if (tid < BS * BS) {
+      int pI, qI, pK, qK;
+      if (st < ninner) {
+        const int eI = ptab[st * BS + I], eK = ptab[st * BS + K];
+        pI = eI & 0xFF; qI = eI >> 8; pK = eK & 0xFF; qK = eK >> 8;
+      } else {
+        const int t = st - ninner;
+        pI = I; qI = BS + ((I + t) & (BS - 1));
+        pK = K; qK = BS + ((K + t) & (BS - 1));
+      }
+      step(st, pI, qI, pK, qK);
+    }
+    __syncthreads();
+  }
+}
+
 template <int JRPL, int NW>
 __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
   using D = JacDims<JRPL, NW>;
@@ -330,91 +425,10 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
         G[(BS + j) * GLD + i] = sxy;
       }
       __syncthreads();
-      // the steps of the round on G and J.  Thread (I, K) of the first BS^2
-      // (I = tid / BS, K = lane % BS) owns the 2 x 2 blocks of G and of J on
-      // the rows of pair I and the columns of pair K (the pairs of a step
-      // partition the 2BS columns, so the blocks partition G and J).  Every
-      // lane computes the rotation of its pair K and takes that of pair I
-      // from a lane of its own row of 16 whose K is I, so one barrier per
-      // step suffices: G is read from one copy and written to the other,
-      // each J block is read and written by its owner only.
-      // A round in which no pair of the block pair passes the rotation test
-      // on the fresh G rotates nothing (G never changes), so its steps are
-      // skipped: the same decisions as running them.  Every sweep's last
-      // round set is such a check.
       int any_pair = 0;
-      for (int e = tid; e < BS * BS; e += NT) {
-        const double tol2 = a.tol * a.tol;
-        const int i = e / BS, j = e % BS;
-        const double gc = G[i * GLD + BS + j];
-        int need = gc * gc > tol2 * (G[i * GLD + i] * G[(BS + j) * GLD + BS + j]);
-        if (r == 0 && i < j) {
-          const double gx = G[i * GLD + j], gy = G[(BS + i) * GLD + BS + j];
-          need |= gx * gx > tol2 * (G[i * GLD + i] * G[j * GLD + j]);
-          need |= gy * gy > tol2 * (G[(BS + i) * GLD + BS + i] * G[(BS + j) * GLD + BS + j]);
-        }
-        any_pair |= need;
-      }
-      const int ninner = (r == 0) ? BS - 1 : 0;
-      const int I = tid / BS, K = tid % BS;
-      const int srcI = (lane & ~(BS - 1)) | I;
-      // one step on the pairs (pI, qI) of thread row I and (pK, qK) of
-      // thread column K, G read from copy st & 1
-      auto step = [&](int st, int pI, int qI, int pK, int qK) {
-        const double* Gc = G + (st & 1) * JJ * GLD;
-        double* Gn = G + ((st + 1) & 1) * JJ * GLD;
-        const double aK = Gc[pK * GLD + pK], bK = Gc[qK * GLD + qK], gK = Gc[pK * GLD + qK];
-        const double gpp = Gc[pI * GLD + pK], gpq = Gc[pI * GLD + qK];
-        const double gqp = Gc[qI * GLD + pK], gqq = Gc[qI * GLD + qK];
-        const double jpp = Jm[pI * GLD + pK], jpq = Jm[pI * GLD + qK];
-        const double jqp = Jm[qI * GLD + pK], jqq = Jm[qI * GLD + qK];
-        double cK = 1.0, sK = 0.0, tK = 0.0;
-        const bool rK = jacobi_rotation_t(aK, bK, gK, a.tol, cK, sK, tK);
-        if (!rK) { cK = 1.0; sK = 0.0; }
-        // (1, 0) for a pair that does not turn: the products below are then
-        // exact copies
-        const double cI = __shfl(cK, srcI, 64), sI = __shfl(sK, srcI, 64);
-        if (I == K) {
-          if (rK) { rotated = 1; rround = 1; }
-          Gn[pK * GLD + pK] = rK ? aK - tK * gK : aK;
-          Gn[qK * GLD + qK] = rK ? bK + tK * gK : bK;
-          Gn[pK * GLD + qK] = rK ? 0.0 : gK;
-          Gn[qK * GLD + pK] = rK ? 0.0 : gK;
-        } else {
-          // rows by the rotation of pair I, then columns by that of pair K
-          const double rpp = cI * gpp - sI * gqp, rqp = sI * gpp + cI * gqp;
-          const double rpq = cI * gpq - sI * gqq, rqq = sI * gpq + cI * gqq;
-          Gn[pI * GLD + pK] = cK * rpp - sK * rpq;
-          Gn[pI * GLD + qK] = sK * rpp + cK * rpq;
-          Gn[qI * GLD + pK] = cK * rqp - sK * rqq;
-          Gn[qI * GLD + qK] = sK * rqp + cK * rqq;
-        }
-        // J <- J J_t on the block: its columns pK, qK turn by pair K
-        if (rK) {
-          Jm[pI * GLD + pK] = cK * jpp - sK * jpq;
-          Jm[pI * GLD + qK] = sK * jpp + cK * jpq;
-          Jm[qI * GLD + pK] = cK * jqp - sK * jqq;
-          Jm[qI * GLD + qK] = sK * jqp + cK * jqq;
-        }
-      };
-      if (__syncthreads_or(any_pair)) {
-#pragma unroll 1
-        for (int st = 0; st < ninner + BS; ++st) {
-          if (tid < BS * BS) {
-            int pI, qI, pK, qK;
-            if (st < ninner) {
-              const int eI = ptab[st * BS + I], eK = ptab[st * BS + K];
-              pI = eI & 0xFF; qI = eI >> 8; pK = eK & 0xFF; qK = eK >> 8;
-            } else {
-              const int t = st - ninner;
-              pI = I; qI = BS + ((I + t) & (BS - 1));
-              pK = K; qK = BS + ((K + t) & (BS - 1));
-            }
-            step(st, pI, qI, pK, qK);
-          }
-          __syncthreads();
-        }
-      }
+      if (tid < BS * BS) any_pair = jac_any_pair(G, tid, r == 0, a.tol);
+      if (__syncthreads_or(any_pair))
+        jac_steps(G, Jm, ptab, tid, lane, (r == 0) ? BS - 1 : 0, a.tol, rotated, rround);
       // W(:, pair) <- W(:, pair) J and V(:, pair) <- V(:, pair) J as
       // W_new^T = J^T W^T (A operand J^T from LDS, B operand the row tiles);
       // lane (c, g) receives rows r0 + c of columns 16 jh + 4 v + g
@@ -482,15 +496,243 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
   }
 }
 
+// ---- the block iteration with every block pair split over 8 workgroups ------
+//
+// A round of jacobi_block_kernel is bound by its one workgroup per block pair:
+// at l = 576 it moves 0.65 MB and does 3.6 MFLOP of FP64 products on one compute
+// unit (12 us at the rate of its matrix cores) beside 16 serial rotation steps
+// (~5 us), 27 us in all, with 18 of 256 compute units at work.  Here workgroup
+// (w, p) owns the rows of the 16-row tiles RTW p .. RTW p + RTW - 1 of pair w:
+// exactly one wave's share of the Gram sums above, so that adding the 8 partial
+// Grams in the order of p gives the same bits.  The parts exchange their partial
+// Grams (6 KB each, agent-scope stores and a tag per tile), every part then runs
+// the same rotation steps on the same G, and applies J to its own rows; part p of
+// the next owner waits for part p only.  The rows of V are not needed before the
+// end of a round: they are loaded while the steps run and written after W is
+// handed over.  29 -> 18 us a round at l = 576 (the rotation steps are 10 of them),
+// 19 -> 16 at l = 220.
+//
+// 4 waves, 47 KB of LDS and at most 168 registers: three workgroups fit on a
+// compute unit, so that the 8 nbp / 2 <= 144 workgroups of one launch, which wait
+// for each other, need 48 of them.
+constexpr int SPLIT = 8;
+
+struct JacSplit {
+  JacArgs j;
+  double* part;         // [2][G][SPLIT][3][256] partial Grams
+  uint32_t* gtags;      // [G][SPLIT] FLAG_STRIDE apart, a word per tile: rounds posted
+  uint32_t* wtags;      // [G][SPLIT] rounds whose rows of W are written
+  uint32_t* vtags;      // [G][SPLIT] the same for V
+};
+
+template <int RTW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void
+jacobi_split_kernel(JacSplit b) {
+  constexpr int NT = 256, NW = 4;
+  constexpr int RP = 16 * RTW;              // rows of a part
+  constexpr int XLD = RP + 1;
+  const JacArgs& a = b.j;
+  __shared__ double Xs[JJ * XLD];           // the part's rows of the pair's columns of W
+  __shared__ double G[2 * JJ * GLD];        // G(i, j) at i GLD + j, two copies
+  __shared__ double Jm[JJ * GLD];           // J(c, j) at c GLD + j
+  __shared__ int ptab[(BS - 1) * BS];       // inner steps: p | q << 8 of pair P in step t
+  __shared__ int rotated, rround;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  const int w = blockIdx.x / SPLIT, p = blockIdx.x % SPLIT;
+  constexpr int LD = SPLIT * RP;            // rows of W and V
+  uint32_t done = 0;
+  int sweep = 0;
+  bool converged = false, dead = false;
+  if (tid == 0) rotated = 0;
+  for (int e = tid; e < (BS - 1) * BS; e += NT) {
+    int pp, q;
+    pair_cols(true, e / BS, e % BS, pp, q);
+    ptab[e] = pp | (q << 8);
+  }
+  // one word of an exchange; after an aborted wait every later one returns
+  auto wait_word = [&](const uint32_t* word, uint32_t target) {
+    uint32_t spins = 0;
+    while (!dead && ld_agent_u32(word) < target + a.wait_bias) {
+      if ((++spins & 63) == 0) {
+        if (ld_agent_u32(a.abort_flag)) dead = true;
+        else if (spins > a.spin_cap) {
+          st_agent_u32(a.abort_flag, 1u);
+          info_or(a.info, INFO_BARRIER);
+          dead = true;
+        }
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  };
+  // whether pair v of round r holds a block that pair w holds in round r + 1
+  auto feeds = [&](int v, int r) {
+    const int nb = a.nbp;
+    const int b1 = rr_player(w, r + 1, nb), b2 = rr_player(nb - 1 - w, r + 1, nb);
+    const int p1 = rr_player(v, r, nb), p2 = rr_player(nb - 1 - v, r, nb);
+    return p1 == b1 || p1 == b2 || p2 == b1 || p2 == b2;
+  };
+  while (!converged && sweep < a.max_sweeps) {
+    for (int r = 0; r < a.nbp - 1; ++r) {
+      // the part's rows of the two blocks' first columns
+      const int bi = __builtin_amdgcn_readfirstlane(rr_player(w, r, a.nbp));
+      const int bj = __builtin_amdgcn_readfirstlane(rr_player(a.nbp - 1 - w, r, a.nbp));
+      const int64_t o0 = (int64_t)bi * (BS * LD) + p * RP, o1 = (int64_t)bj * (BS * LD) + p * RP;
+      // (opaque, so that addresses are formed where they are used and not kept in
+      // registers across the rounds)
+      int l16 = tid & 15, g16 = tid >> 4, lgo = lg;
+      asm volatile("" : "+v"(l16), "+v"(g16), "+v"(lgo));
+      {
+        double u[2][RTW];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const double* pc = a.W + (h ? o1 : o0) + (g16 * LD + l16);
+#pragma unroll
+          for (int t = 0; t < RTW; ++t) u[h][t] = ld_agent(pc + 16 * t);
+        }
+        for (int e = tid; e < JJ * JJ; e += NT)
+          Jm[(e / JJ) * GLD + e % JJ] = (e / JJ == e % JJ) ? 1.0 : 0.0;
+        if (tid == 0) rround = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int t = 0; t < RTW; ++t) Xs[(BS * h + g16) * XLD + 16 * t + l16] = u[h][t];
+      }
+      __syncthreads();
+      // partial Gram tile `wave` (xx, xy, yy) of the part's rows, posted
+      double* const gp = b.part + ((int64_t)(done & 1) * a.G + w) * (SPLIT * 768);
+      if (wave < 3) {
+        d4 acc = Mfma<double>::zero();
+        const double* xa = Xs + (li + (wave == 2 ? BS : 0)) * XLD + lg;
+        const double* xb = Xs + (li + (wave >= 1 ? BS : 0)) * XLD + lg;
+#pragma unroll
+        for (int k = 0; k < 4 * RTW; ++k) acc = Mfma<double>::mma(xa[4 * k], xb[4 * k], acc);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          st_agent(gp + p * 768 + wave * 256 + drow(lg, v) * 16 + li, acc[v]);
+        stores_done();
+        if (lane == 0) st_agent_u32(b.gtags + (w * SPLIT + p) * FLAG_STRIDE + wave, done + 1);
+      }
+      // all partial Grams of the pair; the rows of V of the previous round
+      if (tid < 3 * SPLIT) {
+        wait_word(b.gtags + (w * SPLIT + tid / 3) * FLAG_STRIDE + tid % 3, done + 1);
+      } else if (wave == 1 && lane < a.G && done > 0) {
+        if (r == 0 || feeds(lane, r - 1))
+          wait_word(b.vtags + (lane * SPLIT + p) * FLAG_STRIDE, done);
+      }
+      __syncthreads();
+      {
+        double g[3][SPLIT];
+#pragma unroll
+        for (int q = 0; q < SPLIT; ++q)
+#pragma unroll
+          for (int t = 0; t < 3; ++t) g[t][q] = ld_agent(gp + q * 768 + t * 256 + tid);
+        double sum[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < SPLIT; ++q)
+#pragma unroll
+          for (int t = 0; t < 3; ++t) sum[t] += g[t][q];
+        const int i = tid / 16, j = tid % 16;
+        G[i * GLD + j] = sum[0];
+        G[(BS + i) * GLD + BS + j] = sum[2];
+        G[i * GLD + BS + j] = sum[1];
+        G[(BS + j) * GLD + i] = sum[1];
+      }
+      // the operands of V's product, V(row, col 4 kk + lg) of row tile t: the
+      // wave's first tile in flight during the steps
+      double vu[8];
+      auto load_v = [&](int t) {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk)
+          vu[kk] = ld_agent(a.V + (kk < 4 ? o0 : o1) + (4 * (kk & 3) * LD) + 16 * t +
+                            (lgo * LD + l16));
+      };
+      if (wave < RTW) load_v(wave);
+      jac_lds_barrier();
+      if (__syncthreads_or(jac_any_pair(G, tid, r == 0, a.tol))) {
+        const int ninner = (r == 0) ? BS - 1 : 0;
+        jac_steps(G, Jm, ptab, tid, lane, ninner, a.tol, rotated, rround);
+      }
+      const bool last = (r == a.nbp - 2);
+      if (last && p == 0 && tid == 0)
+        st_agent_u32(a.rot + ((sweep & 1) * a.G + w) * FLAG_STRIDE, (uint32_t)rotated);
+      // W(:, pair) <- W(:, pair) J, V(:, pair) <- V(:, pair) J on the part's rows
+      const bool turn = rround != 0;
+      if (turn) {
+        // (row tile, half of the columns) tasks: wave q takes q, q + 4, ...; a
+        // wave's half is fixed
+        const int jh = wave & 1;
+        double jw[8];
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) jw[kk] = Jm[(4 * kk + lg) * GLD + 16 * jh + li];
+#pragma unroll
+        for (int t = wave >> 1; t < RTW; t += 2) {
+          d4 acc = Mfma<double>::zero();
+#pragma unroll
+          for (int kk = 0; kk < 8; ++kk)
+            acc = Mfma<double>::mma(jw[kk],
+                                    Xs[(4 * kk + lg) * XLD + 16 * t + li], acc);
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            st_agent(a.W + (jh ? o1 : o0) + 4 * v * LD + 16 * t + (lgo * LD + l16), acc[v]);
+        }
+      }
+      stores_done();
+      __syncthreads();
+      ++done;
+      if (tid == 0) st_agent_u32(b.wtags + (w * SPLIT + p) * FLAG_STRIDE, done);
+      if (turn) {
+        for (int t = wave; t < RTW; t += NW) {
+          if (t >= NW) load_v(t);
+#pragma unroll
+          for (int jh = 0; jh < 2; ++jh) {
+            d4 acc = Mfma<double>::zero();
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk)
+              acc = Mfma<double>::mma(Jm[(4 * kk + lg) * GLD + 16 * jh + li], vu[kk], acc);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              st_agent(a.V + (jh ? o1 : o0) + 4 * v * LD + 16 * t + (lgo * LD + l16), acc[v]);
+          }
+        }
+      }
+      // The part's rows of W of the next round (at a sweep's end also every
+      // pair's rotation flag); the stores to V are done by the barrier
+      if (tid < a.G) {
+        if (last || feeds(tid, r)) wait_word(b.wtags + (tid * SPLIT + p) * FLAG_STRIDE, done);
+      } else if (last && wave == 1 && lane < a.G) {
+        wait_word(b.wtags + lane * SPLIT * FLAG_STRIDE, done);
+      }
+      stores_done();
+      __syncthreads();
+      if (tid == 0) st_agent_u32(b.vtags + (w * SPLIT + p) * FLAG_STRIDE, done);
+    }
+    // every workgroup reads the same flags, so all take the same decision
+    const uint32_t rot =
+        tid < a.G ? ld_agent_u32(a.rot + ((sweep & 1) * a.G + tid) * FLAG_STRIDE) : 0u;
+    ++sweep;
+    converged = __syncthreads_or(rot != 0) == 0;
+    if (tid == 0) rotated = 0;
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    if (!converged) info_or(a.info, INFO_JACOBI_CAP);
+    if (a.sweeps_out) *a.sweeps_out = sweep;
+  }
+}
+
 // W = Rh (column j of W is row j of the row-major Rh), V = I, both padded
 // with zeros to ld rows and ncols columns
 __global__ __launch_bounds__(256) void jacobi_init_kernel(const double* __restrict__ Rh,
                                                           int64_t ldr, int l, int ncols,
                                                           double* __restrict__ W,
                                                           double* __restrict__ V, int64_t ld,
-                                                          uint32_t* ctl, int nctl) {
+                                                          uint32_t* ctl, int nctl,
+                                                          uint32_t* xtags, int nxtags) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e < nctl) ctl[e] = 0;
+  if (e < nxtags) xtags[e] = 0;
   if (e >= ld * ncols) return;
   const int j = (int)(e / ld), i = (int)(e - (int64_t)j * ld);
   const bool in = i < l && j < l;
@@ -564,6 +806,14 @@ size_t jacobi_work_bytes(int l) {
          JCTL * FLAG_STRIDE * sizeof(uint32_t) + (size_t)l * sizeof(double) + 256;
 }
 
+// the exchange area of the split iteration: partial Grams, then three sets of tags
+static size_t split_words(int G) { return (size_t)3 * G * SPLIT * FLAG_STRIDE; }
+size_t jacobi_exchange_bytes(int l) {
+  if (l <= LDS_MAX_L) return 0;
+  const int G = jac_cols(l) / BS / 2;
+  return (size_t)2 * G * SPLIT * 768 * sizeof(double) + split_words(G) * sizeof(uint32_t);
+}
+
 template <int JRPL, int NW>
 hipError_t launch_block(JacArgs& a, hipStream_t s) {
   const size_t shm = JacDims<JRPL, NW>::LDS;
@@ -577,7 +827,8 @@ hipError_t launch_block(JacArgs& a, hipStream_t s) {
 
 hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* work, double* S,
                          double* Uh, int64_t lduh, double* Vh, int64_t ldvh, int max_sweeps,
-                         int32_t* info, int32_t* sweeps_out, bool giveup_test, hipStream_t s) {
+                         int32_t* info, int32_t* sweeps_out, bool giveup_test, hipStream_t s,
+                         double* xch, size_t xch_bytes, int ncu) {
   if (l > JACOBI_MAX_L) return hipErrorInvalidValue;
   const double tol = (double)l * 2.220446049250313e-16;
   if (l <= LDS_MAX_L) {
@@ -608,13 +859,32 @@ hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* wo
   a.spin_cap = giveup_test ? (1u << 10) : (1u << 22);
   a.info = info;
   a.sweeps_out = sweeps_out;
+  // Split where the caller lends the exchange area and 8 workgroups per pair find
+  // room at two to a compute unit (three fit); beside a pivoted QR, which takes
+  // all but a few compute units, a pair has one workgroup.
+  const bool split = xch && xch_bytes >= jacobi_exchange_bytes(l) && a.G * SPLIT <= 2 * ncu;
+  JacSplit b;
+  b.j = a;
+  b.part = xch;
+  b.gtags = reinterpret_cast<uint32_t*>(xch + (size_t)2 * a.G * SPLIT * 768);
+  b.wtags = b.gtags + a.G * SPLIT * FLAG_STRIDE;
+  b.vtags = b.wtags + a.G * SPLIT * FLAG_STRIDE;
+  const int nx = split ? (int)split_words(a.G) : 0;
   // one thread per element of W and per control word
-  const int64_t ninit = std::max<int64_t>(ld * ncols, (int64_t)JCTL * FLAG_STRIDE);
+  const int64_t ninit =
+      std::max<int64_t>(ld * ncols, std::max<int64_t>((int64_t)JCTL * FLAG_STRIDE, nx));
   hipLaunchKernelGGL(jacobi_init_kernel, dim3((unsigned)cdiv(ninit, 256)), dim3(256), 0, s, Rh,
-                     ldr, l, ncols, W, V, ld, ctl, JCTL * FLAG_STRIDE);
+                     ldr, l, ncols, W, V, ld, ctl, JCTL * FLAG_STRIDE, b.gtags, nx);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = (l <= 256) ? launch_block<16, 8>(a, s) : launch_block<40, 8>(a, s);
+  if (split) {
+    const dim3 grid((unsigned)(a.G * SPLIT));
+    if (l <= 256) hipLaunchKernelGGL(jacobi_split_kernel<2>, grid, dim3(256), 0, s, b);
+    else hipLaunchKernelGGL(jacobi_split_kernel<5>, grid, dim3(256), 0, s, b);
+    e = hipGetLastError();
+  } else {
+    e = (l <= 256) ? launch_block<16, 8>(a, s) : launch_block<40, 8>(a, s);
+  }
   if (e != hipSuccess) return e;
   double* sig = reinterpret_cast<double*>(ctl + JCTL * FLAG_STRIDE);
   const unsigned nwg = (unsigned)cdiv(l, JOW);

@@ -519,7 +519,8 @@ hipError_t run_decompose(Ctx& c, const Shape& s, const Bufs& b, const void* A, i
       s1 = c.h->aux;
     }
     RSVD_TRY(launch_jacobi(b.Rh, lp, l, k, b.Wj, o.S, b.Uh, s.kp, b.Vh, s.kp,
-                           c.h->jacobi_max_sweeps, c.info, nullptr, c.h->giveup_test, s1));
+                           c.h->jacobi_max_sweeps, c.info, nullptr, c.h->giveup_test, s1,
+                           fork ? nullptr : b.ob.gpart, gram_part_bytes(lp, NCU_CAP), ncu));
     const GemmPlan pu = plan_gemm(m, l, k, ncu, 0);
     RSVD_TRY(launch_gemm(f32 ? GEMM_FDDF : GEMM_DDDD, false, b.Q, lp, b.Vh, s.kp, o.U, o.ldu, m, l,
                          k, pu, b.ob.part, b.ob.part_bytes, s1));
@@ -838,7 +839,8 @@ hipError_t run_grad(Ctx& c, const Shape& s, const GradBufs& g, const double* A, 
   RSVD_TRY(pass(c, 0, true, m, n, l, A, lda, g.Q, lp, g.Zt, lp, ob.part, ob.part_bytes));
   RSVD_TRY(orth(c, ob, false, g.Zt, lp, n, l, g.Qh, false, lp, g.Rh, lp));
   RSVD_TRY(launch_jacobi(g.Rh, lp, l, l, g.Wj, g.sv, g.Uh, lp, g.Vh, lp, c.h->jacobi_max_sweeps,
-                         c.info, nullptr, c.h->giveup_test, c.st));
+                         c.info, nullptr, c.h->giveup_test, c.st, ob.gpart,
+                         gram_part_bytes(lp, NCU_CAP), std::min(c.ncu, NCU_CAP)));
   if (io.U) RSVD_TRY(small_gemm(c, ob, false, g.Q, lp, g.Vh, lp, io.U, io.ldu, m, l, k));
   if (io.V) RSVD_TRY(small_gemm(c, ob, false, g.Qh, lp, g.Uh, lp, io.V, io.ldv, n, l, k));
   if (io.S)
@@ -1719,7 +1721,7 @@ int rsvd_orth(rsvd_handle_t h, int dtype, int64_t rows, int64_t l, const void* Y
 
 size_t rsvd_small_svd_workspace_bytes(int64_t l) {
   if (l < 1 || l > MAX_L_SVD) return 0;
-  return jacobi_work_bytes((int)l) + sizeof(int32_t) + 256;
+  return jacobi_work_bytes((int)l) + jacobi_exchange_bytes((int)l) + sizeof(int32_t) + 1024;
 }
 
 int rsvd_small_svd(rsvd_handle_t h, int64_t l, int k, const double* Rh, int64_t ldr, double* S,
@@ -1743,10 +1745,12 @@ int rsvd_small_svd(rsvd_handle_t h, int64_t l, int k, const double* Rh, int64_t 
   hipStream_t st = static_cast<hipStream_t>(stream);
   Arena a(work);
   double* jw = a.take<double>(jacobi_work_bytes((int)l) / sizeof(double) + 1);
+  const size_t xb = jacobi_exchange_bytes((int)l);
+  double* xch = a.take<double>(xb / sizeof(double));
   hipError_t e = launch_reset(info, nullptr, nullptr, st);
   if (e == hipSuccess)
     e = launch_jacobi(Rh, ldr, (int)l, k, jw, S, Uh, lduh, Vh, ldvh, h->jacobi_max_sweeps, info,
-                      nullptr, h->giveup_test, st);
+                      nullptr, h->giveup_test, st, xch, xb, std::min(h->ncu, NCU_CAP));
   return finish(e);
 }
 

@@ -142,3 +142,55 @@ def test_cpqr_ties_take_the_lowest_column(R):
     B[:, [8000, 300, 299]] = 0.5 * y[:, None]
     J, T, pv, info = R.cpqr(dev(B.T), r, 2)
     assert J.cpu().numpy()[:2].tolist() == [66, 299]
+
+
+# ---- the block Jacobi split over workgroups ------------------------------------
+# one more column than the single-workgroup limit, around the blocks of 16, an odd
+# number of blocks, both row layouts (l <= 256 and above), the largest
+@pytest.mark.parametrize("l", [65, 80, 81, 112, 256, 257, 400, 576])
+def test_small_svd_split(R, l):
+    g = np.random.default_rng(l)
+    U0 = np.linalg.qr(g.standard_normal((l, l)))[0]
+    V0 = np.linalg.qr(g.standard_normal((l, l)))[0]
+    so = np.logspace(0, -3, l)
+    Rh = np.linalg.qr((U0 * so) @ V0.T)[1]
+    S, Uh, Vh, info = R.small_svd(dev(Rh), l)
+    S, Uh, Vh = S.cpu().numpy(), Uh.cpu().numpy(), Vh.cpu().numpy()
+    assert int(info.cpu()[0]) == 0
+    # the rounding of l rotations per column and sweep, of the size of sigma_1
+    bound = 50 * l * np.finfo(np.float64).eps
+    assert np.abs(S - so).max() <= bound
+    assert orth_err(Uh) <= bound * 1e3 and orth_err(Vh) <= bound     # (Uh: w_j / sigma_j)
+    assert np.abs(Rh @ Vh - Uh * S[None, :]).max() <= bound
+
+
+@pytest.mark.parametrize("l", [70, 112, 256])
+def test_split_and_whole_pairs_give_the_same_bits(R, l):
+    """svd splits the block pairs; beside a pivoted QR (decompose) each has one
+    workgroup: the sums have the same order."""
+    g = torch.Generator(device="cuda").manual_seed(l)
+    A = torch.randn((700, 400), dtype=torch.float64, device="cuda", generator=g)
+    k, p = l - 10, 10
+    U, S, V, info = R.svd(A, k, p, 1, 5)
+    D = R.decompose(A, k, p, 1, 5)
+    assert int(info.cpu()[0]) == 0
+    for x, y in ((U, D["U"]), (S, D["S"]), (V, D["V"])):
+        assert torch.equal(x, y)
+
+
+def test_split_jacobi_on_four_streams(R):
+    g = torch.Generator(device="cuda").manual_seed(9)
+    As = [torch.randn((1500, 1200), dtype=torch.float64, device="cuda", generator=g)
+          for _ in range(4)]
+    alone = [R.svd(A, 560, 16, 0, 3) for A in As]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in As]
+    beside = []
+    for A, s in zip(As, streams):
+        with torch.cuda.stream(s):
+            beside.append(R.svd(A, 560, 16, 0, 3))
+    torch.cuda.synchronize()
+    for x, y in zip(alone, beside):
+        assert int(y[3].cpu()[0]) == 0
+        for u, v in zip(x[:3], y[:3]):
+            assert torch.equal(u, v)
