@@ -88,6 +88,30 @@ __device__ __forceinline__ d4 load_gtile(const double* G, int64_t ldg, int l, in
   return t;
 }
 
+// Row broadcasts (DPP row_newbcast, the form that FP64 operations take): lane L of
+// every row of 16 lanes.  A register that a VALU operation wrote is not read through
+// DPP within two wait states: dpp_source stands between (bcast has its own).
+__device__ __forceinline__ void dpp_source(double& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 1" : "+v"(x));
+#endif
+}
+template <int L> __device__ __forceinline__ double bcast(double x) {
+  double d = x;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
+      : "=v"(d) : "v"(x), "n"(L));
+#endif
+  return d;
+}
+// acc = fma(-(r of lane L), y, acc)
+template <int L> __device__ __forceinline__ void fnma_bcast(double& acc, double r, double y) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+      : "+v"(acc) : "v"(r), "v"(y), "n"(L));
+#endif
+}
+
 // Right-looking block Cholesky with a one-step lookahead, one workgroup of
 // NW waves.  Waves 1 .. NW-1 hold the upper 16x16 tiles of G in matrix-core
 // accumulator layout (tile t of the row-major enumeration of the upper
@@ -117,7 +141,6 @@ __device__ __forceinline__ void chol_factor(const double* G, int64_t ldg, int l,
   __shared__ double Dw[16 * 17];        // wave 0: the updated diagonal tile
   __shared__ double Rs[16 * 16];        // R_ss, row-major
   __shared__ double Xs[16 * 16];        // R_ss^{-1}, row-major
-  __shared__ double dinvs[16];          // 1 / R_ss[j][j]
   __shared__ double diag0[256];
   __shared__ int depblk[16];
 
@@ -190,62 +213,65 @@ __device__ __forceinline__ void chol_factor(const double* G, int64_t ldg, int l,
       // subtracts R[j][a] R[j][c] from the rows a > j.  Lanes c < j compute
       // values that are never read (rows below the diagonal are dropped at
       // the end).  A column whose pivot is not above eta * G_jj gets a unit
-      // row.
+      // row.  Entries of other lanes come by row broadcasts inside the FMAs
+      // (fnma_bcast): with two readlanes per entry and a store per step a step took
+      // 430 cycles, and it takes 250.
       const double thr = eta * diag0[s * 16 + c];
-      uint32_t okm = 0u, nfm = 0u;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const double d = readlane_d(x[j], j);
+      double inv[16];
+      bool okc = true, nfc = false;      // of the lane's own column
+      static_for<16>([&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        const double d = bcast<j>(x[j]);
         const bool finite = __builtin_isfinite(d);
-        const bool ok = finite && d > readlane_d(thr, j);
-        okm |= ok ? (1u << j) : 0u;
-        nfm |= finite ? 0u : (1u << j);
+        const bool ok = finite && d > bcast<j>(thr);
+        okc = c == j ? ok : okc;
+        nfc = c == j ? !finite : nfc;
         // branch-free: the estimate is formed for any d and then selected
         const double inv0 = rsq_nr(d);
-        const double inv = ok ? inv0 : 1.0;
-        const double r = ok ? x[j] * inv0 : ((c == j) ? 1.0 : 0.0);
+        inv[j] = ok ? inv0 : 1.0;
+        double r = ok ? x[j] * inv0 : ((c == j) ? 1.0 : 0.0);
+        dpp_source(r);
         x[j] = r;
-        if (lane == 0) dinvs[j] = inv;
-#pragma unroll
-        for (int a = j + 1; a < 16; ++a) x[a] = fma(-readlane_d(r, a), r, x[a]);
-      }
+        static_for<15 - j>([&](auto ii) {
+          constexpr int a = j + 1 + decltype(ii)::value;
+          fnma_bcast<a>(x[a], r, r);
+        });
+      });
       // R_ss to LDS (the four row groups of the wave hold the same columns
       // and store the same values); the update waves copy it to R in phase 2
 #pragma unroll
       for (int a = 0; a < 16; ++a) Rs[a * 16 + c] = (a <= c) ? x[a] : 0.0;
       if (lane < 16) {
-        const int dj = ((okm >> c) & 1u) ? 0 : 1;
+        const int dj = okc ? 0 : 1;
         depblk[c] = dj;
         if (s * 16 + c < l) dep[s * 16 + c] = dj;
       }
+      // columns of the block below l that failed the test
+      const uint64_t bad = __ballot(lane < 16 && s * 16 + c < l && !okc);
+      const uint64_t nf = __ballot(nfc);
       if (lane == 0) {
-        // columns of the block below l that failed the test
-        const uint32_t lmask = (l - s * 16 >= 16) ? 0xFFFFu : ((1u << (l - s * 16)) - 1u);
-        const uint32_t bad = ~okm & lmask;
-        if ((bad & nfm) != 0u) info_or(info, INFO_NONFINITE);
-        if ((bad & ~nfm) != 0u) info_or(info, INFO_ORTH_FALLBACK);
+        if ((bad & nf) != 0u) info_or(info, INFO_NONFINITE);
+        if ((bad & ~nf) != 0u) info_or(info, INFO_ORTH_FALLBACK);
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       // X = R_ss^{-1}, column c in lane c by back substitution (the entries
-      // below the diagonal come out zero).  Row a of R is read from LDS (the
-      // same address in every lane); the terms of rows b > a+1 are summed in
-      // two chains before X[a+1] is known, so each row adds one product to
-      // the dependent chain.
+      // below the diagonal come out zero), R[a][b] broadcast from lane b; the terms
+      // of rows b > a+1 are summed in two chains before X[a+1] is known, so each
+      // row adds one product to the dependent chain (250 -> 190 cycles a row against
+      // reads of R from LDS).
       double X[16];
-#pragma unroll
-      for (int a = 15; a >= 0; --a) {
+      static_for<16>([&](auto ii) { dpp_source(x[decltype(ii)::value]); });
+      static_for<16>([&](auto ii) {
+        constexpr int a = 15 - decltype(ii)::value;
         double u0 = (a == c) ? 1.0 : 0.0, u1 = 0.0;
-#pragma unroll
-        for (int b = 15; b > a + 1; --b) {
-          if ((b & 1) == 0) u0 = fma(-Rs[a * 16 + b], X[b], u0);
-          else u1 = fma(-Rs[a * 16 + b], X[b], u1);
-        }
+        static_for<(a < 14 ? 14 - a : 0)>([&](auto kk) {
+          constexpr int b = 15 - decltype(kk)::value;      // 15 .. a + 2
+          if constexpr ((b & 1) == 0) fnma_bcast<b>(u0, x[a], X[b]);
+          else fnma_bcast<b>(u1, x[a], X[b]);
+        });
         double u = u0 + u1;
-        if (a < 15) u = fma(-Rs[a * 16 + a + 1], X[a + 1], u);
-        X[a] = u * dinvs[a];
-      }
+        if constexpr (a < 15) fnma_bcast<a + 1>(u, x[a], X[a + 1]);
+        X[a] = u * inv[a];
+      });
 #pragma unroll
       for (int a = 0; a < 16; ++a) Xs[a * 16 + c] = X[a];
       __syncthreads();
