@@ -43,8 +43,7 @@ def time_shape(R, torch, ms, ns, ks, buf, shape):
 def main(argv=None):
     ap = argparse.ArgumentParser(description=__doc__)
     ap.add_argument("--out", default=BT.TABLE_PATH)
-    # (two per workgroup at two workgroups per compute unit)
-    ap.add_argument("--count", type=int, default=1024, help="matrices per bucket batch")
+    ap.add_argument("--count", type=int, default=256, help="matrices per bucket batch")
     args = ap.parse_args(argv)
     import torch
     import paper_1502_05366_amd as R
