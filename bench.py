@@ -38,9 +38,9 @@ PEAK_FP8_TFLOPS = 5000.0
 # FETCH_SIZE and WRITE_SIZE counters of two rocprofv3 --pmc runs of this
 # script, each scaled by counter/bytes of the plain 1 GiB copy kernel timed
 # below; valid only while the pass kernel's sources hash to "sources".
-PASS_TRAFFIC = {"sources": "fc2a4138c2a8871c57e6d256b627da01351229dcf28ef61f39e02b7dbe4b90c7",
-                "bytes": 4589000000}
-PASS_SOURCES = ("paper_1502_05366_amd/csrc/gemm.hip",)
+PASS_TRAFFIC = {"sources": "926145c77b7f8bd3f1a13bd33774d4c2a10a38b6c7b39bb3d43e37de41f4ebf2",
+                "bytes": 4615000000}
+PASS_SOURCES = ("paper_1502_05366_amd/csrc/gemm.hip", "paper_1502_05366_amd/csrc/gemm_reg.h")
 
 
 def pass_sources_hash():
@@ -425,7 +425,7 @@ def batch_step(lib, args, stream, e0, e1):
             "a_traffic_GBs": round(abytes / (ms_graph * 1e-3) / 1e9, 1),
             "a_bytes_per_batch": abytes, "info": [int(st[0]), int(st[1])],
             "workload": "4096 FP32 matrices, m~U{64..2048}, n~U{64..1024}, k~U{4..64}, "
-                        "p=8, q=1, sigma_j=exp(-j/8); one persistent launch per batch",
+                        "p=8, q=1, sigma_j=exp(-j/8); one rsvd_batch_svd call per batch",
             "note": "GFLOP/s = sum over matrices of 2(2q+2)mnl + (q+1)(2ml^2-2l^3/3) + "
                     "(q+1)(2nl^2-2l^3/3) + 2(m+n)lk per graph replay; a_traffic = (2q+2) "
                     "reads of every A_i per replay"}
@@ -933,7 +933,7 @@ def main():
                      "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_FP64_TFLOPS, 4), "traffic": pass_traffic(),
                      "traffic_unit": "bytes per pass",
-                     "kernel": "pass over A (gemm_sk_kernel + fix-up), FP64 MFMA 16x16x4",
+                     "kernel": "pass over A (gemmreg::kernel + fix-up), FP64 MFMA 16x16x4",
                      "pass_ms": {kk: round(v, 4) for kk, v in pass_ms.items()},
                      "pass_hbm_GBs": round(a_bytes / (t_pass * 1e-3) / 1e9, 1),
                      "copy_kernel_GBs": round(copy_gbs, 1)},

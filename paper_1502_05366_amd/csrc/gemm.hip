@@ -404,7 +404,8 @@ GemmPlan plan_gemm(int64_t M, int64_t K, int64_t L, int ncu, int force_G) {
     if (G < T) G = T;
     // narrow products (l <= 64) are bound by HBM latency: two workgroups per
     // compute unit keep more loads in flight (measured at l = 30 on a
-    // 20000 x 10000 FP64 A: 3.0 -> 3.5 TB/s for A X, 3.2 -> 4.0 for A^T X)
+    // 20000 x 10000 FP64 A with A staged in LDS: 3.0 -> 3.5 TB/s for A X, 3.2 ->
+    // 4.0 for A^T X)
     const int64_t gmax = p.cbw <= 2 ? 2 * (int64_t)ncu : ncu;
     if (G > gmax) G = gmax;
     p.G = G;
