@@ -254,7 +254,7 @@ int rsvd_svd_grad(rsvd_handle_t h, int dtype, int64_t m, int64_t n, int k, int p
 /* Batched randomized SVD: `count` independent FP32 matrices A_i (m_i x n_i,
  * rank k_i, the same p and q), each decomposed as by rsvd_svd (Alg. 5 with
  * re-orthonormalization after every product, Sec. 3.2; the small SVD from the
- * QR of B_i^T) in one persistent launch: the workgroups take matrices from a
+ * QR of B_i^T) in persistent launches: the workgroups take matrices from a
  * work queue in decreasing order of work, one matrix per workgroup at a time
  * (the matrices are independent, as the blocks of Alg. 8 are).  Omega_i is
  * Philox stream 0 with batch index i under the call's seed.  Limits:

@@ -12,7 +12,7 @@ used for device memory and streams.  Names follow the C entry points:
     cur(A, k, p, q, seed)        -> Jc, Jr, U, info    (CUR from the two-sided ID)
     svd_grad(A, k, p, q, seed, dU, dS, dV, dres) -> dA (adjoint, sketch fixed)
     svd_diff(A, k, p, q, seed)   -> U, S, V, resid2    (torch.autograd.Function)
-    BatchPlan(ms, ns, ks, p, q)  -> batched RSVD of FP32 matrices in one persistent launch
+    BatchPlan(ms, ns, ks, p, q)  -> batched RSVD of FP32 matrices in persistent launches
     decompose(A, k, p, q, seed)  -> dict with all three from one range finder
 
     svd_ex(A, k, p, q, seed, scales, want_Q) -> U, S, V, info, Q (also FP8 A with column scales)
