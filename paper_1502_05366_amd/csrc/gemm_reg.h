@@ -110,9 +110,15 @@ __device__ __forceinline__ int opaque_zero() {
   asm volatile("v_mov_b32 %0, 0" : "=v"(z));
   return z;
 }
-__device__ __forceinline__ void settle2() { asm volatile("s_nop 1" ::: "memory"); }
+// a step's A (r.v), which vector instructions wrote, two wait states later: tied to the
+// registers (a bare wait may move to before the writes)
+template <typename R> __device__ __forceinline__ void settle_operands(R& r) {
+#pragma unroll
+  for (int i = (int)(sizeof(r.v) / sizeof(r.v[0])) - 1; i > 0; --i) asm volatile("" : "+v"(r.v[i]));
+  asm volatile("s_nop 1" : "+v"(r.v[0]));
+}
 #else   // (the host pass does not know the register constraints)
-__device__ void settle2();
+template <typename R> __device__ void settle_operands(R& r);
 __device__ int opaque_zero();
 template <bool AC> __device__ void mma(d4& acc, double a, double b);
 template <bool AC> __device__ void mma(f4& acc, float a, float b);
@@ -399,7 +405,7 @@ __global__ __launch_bounds__(NT)
         const int b1 = b == NS - 1 ? 0 : b + 1, b2 = b1 == NS - 1 ? 0 : b1 + 1;
         const int64_t ta = min(t + 3, lastf), tx = min(t + 4, lastf);
         deal(ra[S]);
-        settle2();
+        settle_operands(ra[S]);
         step(ra[S], b, b1, (S * NG) & 1, [&](int e) {
           if (e < NA) aload1(ra[(S + 3) % 4], e, ta);
           else if (e < NA + XPT) xstore1(rx[S % 2], e - NA, b2);
@@ -419,7 +425,7 @@ __global__ __launch_bounds__(NT)
         const int b1 = b == NS - 1 ? 0 : b + 1, b2 = b1 == NS - 1 ? 0 : b1 + 1;
         const int64_t ta = min(t + 3, lastf), tx = min(t + 4, lastf);
         if (t <= lastf) deal(ra[0]);
-        settle2();
+        settle_operands(ra[0]);
         step(ra[0], b, b1, 0, [&](int e) {
           if (e < NA) aload1(ra[3], e, ta);
           else if (e < NA + XPT) xstore1(rx[0], e - NA, b2);
