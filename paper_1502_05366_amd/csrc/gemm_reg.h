@@ -15,8 +15,10 @@
 //    products.  One barrier per step, which no wave reaches before its
 //    products are issued.
 //  * Loads, LDS stores and operand reads are spread over the products.
-//  * The accumulators stay in the accumulation registers (assembly products:
-//    through the builtins the register allocator moves them inside the loop).
+//  * The accumulators stay in the accumulation registers through the k loop
+//    (assembly products: through the builtins the register allocator moves them
+//    inside it).  The waits around these products are in the source (settle,
+//    settle_operands), tied to the registers that they stand for.
 //
 // Products (16 x 16 x 4; lane l, g = l / 16, c = l % 16): A operand A[row c][k g],
 // B operand X[k g][col c].  A product sums over k in any order, so k is dealt to
@@ -99,30 +101,53 @@ template <bool AC> __device__ __forceinline__ void mma(f4& acc, float a, float b
   if constexpr (AC) asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
   else asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
-// ordinary writes of operands / of the accumulators have settled (the
-// compiler does not see the matrix instructions: two wait states before them,
-// their own length after the last one)
-__device__ __forceinline__ void settle() {
+// Wait states that the compiler does not insert, since it does not see the matrix
+// instructions: two between a vector instruction and the products that read what it
+// wrote, their own length (19 states in FP64, 10 in FP32) between the last products
+// and a read of the accumulators.  Each is tied to the registers it stands for: a
+// bare wait leaves the compiler free to move their other accesses across it.
+template <bool AC, typename V> __device__ __forceinline__ void tie(V& x) {
+  if constexpr (AC) asm volatile("" : "+a"(x));
+  else asm volatile("" : "+v"(x));
+}
+// the accumulators: what was written before is read by the products after this, and
+// the results of the products before are there after it
+template <bool AC, typename V, int S, int N>
+__device__ __forceinline__ void settle(V (&acc)[S][2][N]) {
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) tie<AC>(acc[s][i / N][i % N]);
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int i = 0; i < 2 * N; ++i) tie<AC>(acc[s][i / N][i % N]);
 }
 __device__ __forceinline__ int opaque_zero() {
   int z;
   asm volatile("v_mov_b32 %0, 0" : "=v"(z));
   return z;
 }
-// a step's A (r.v), which vector instructions wrote, two wait states later: tied to the
-// registers (a bare wait may move to before the writes)
+// a step's A
 template <typename R> __device__ __forceinline__ void settle_operands(R& r) {
 #pragma unroll
   for (int i = (int)(sizeof(r.v) / sizeof(r.v[0])) - 1; i > 0; --i) asm volatile("" : "+v"(r.v[i]));
   asm volatile("s_nop 1" : "+v"(r.v[0]));
 }
+// a column group's X
+template <typename V> __device__ __forceinline__ void settle_operands(V (&x)[4]) {
+#pragma unroll
+  for (int i = 3; i > 0; --i) tie<false>(x[i]);
+  asm volatile("s_nop 1" : "+v"(x[0]));
+}
 #else   // (the host pass does not know the register constraints)
 template <typename R> __device__ void settle_operands(R& r);
+template <typename V> __device__ void settle_operands(V (&x)[4]);
 __device__ int opaque_zero();
 template <bool AC> __device__ void mma(d4& acc, double a, double b);
 template <bool AC> __device__ void mma(f4& acc, float a, float b);
-__device__ void settle();
+template <bool AC, typename V, int S, int N> __device__ void settle(V (&acc)[S][2][N]);
 #endif
 
 __device__ __forceinline__ int64_t range_begin(int64_t w, int64_t U, int64_t G) {
@@ -232,9 +257,13 @@ __global__ __launch_bounds__(NT)
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) ap[rb] = A + min(m0 + 16 * rb + c, g.M - 1) * g.lda + KN * q;
     }
-    const T* xp[XPT];
+    // (one address where a thread's pairs lie in one column, XR rows apart: with one
+    // per pair the 16 blocks of FP32 do not fit, and an accumulator block left the
+    // accumulation registers in every step)
+    constexpr int XR = NT % (BN / 2) == 0 ? NT / (BN / 2) : 0;
+    const T* xp[XR ? 1 : XPT];
 #pragma unroll
-    for (int i = 0; i < XPT; ++i) {
+    for (int i = 0; i < (XR ? 1 : XPT); ++i) {
       const int ch = tid + i * NT;
       const int64_t col = col0 + 2 * (ch % (BN / 2));
       xp[i] = X + (ch < XP ? ch / (BN / 2) : 0) * g.ldx + (col < g.L ? col : 0);
@@ -246,7 +275,7 @@ __global__ __launch_bounds__(NT)
             ap[i / (NA / 2)] + kt * BK + 4 * KN * (i % (NA / 2)));
     };
     auto xload1 = [&](u2 (&rx)[XPT], int i, int64_t kt) {
-      rx[i] = *reinterpret_cast<const u2*>(xp[i] + kt * BK * g.ldx);
+      rx[i] = *reinterpret_cast<const u2*>(xp[XR ? 0 : i] + (kt * BK + XR * i) * g.ldx);
     };
     auto xstore1 = [&](const u2 (&rx)[XPT], int i, int b) {
       const int ch = tid + i * NT;
@@ -359,10 +388,13 @@ __global__ __launch_bounds__(NT)
       xstore_last(kb == lastf ? 1 : 0);
       if (kb > lastf) aload_last(ra[0]);
     }
-    if (!DEEP && kb <= lastf) deal(ra[0]);
+    if constexpr (!DEEP) {
+      if (kb <= lastf) deal(ra[0]);
+      settle_operands(ra[0]);
+    }
     __syncthreads();
     bread(0, 0, 0);
-    settle();
+    settle<!DEEP>(acc);
     int b = 0;
     if constexpr (!DEEP) {
       // Step t: the loads of A for t + 1 and of X for t + 2 go out in its first
@@ -385,10 +417,12 @@ __global__ __launch_bounds__(NT)
           if (t + 1 == lastf) xstore_last(b2);
           else if (t == lastf) aload_last(ra[0]);
         }
+        settle_operands(ra[0]);
         b = b1;
         if (NG & 1) {
 #pragma unroll
           for (int p = 0; p < 4; ++p) bq[0][p] = bq[1][p];
+          settle_operands(bq[0]);
         }
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
@@ -442,12 +476,13 @@ __global__ __launch_bounds__(NT)
         if (NG & 1) {
 #pragma unroll
           for (int p = 0; p < 4; ++p) bq[0][p] = bq[1][p];
+          settle_operands(bq[0]);
         }
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
       }
     }
-    settle();
+    settle<!DEEP>(acc);
     if constexpr (SETS == 4) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)

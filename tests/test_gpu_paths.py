@@ -68,6 +68,21 @@ def test_pass_short_steps(R, m, n, l, dtype):
     assert np.array_equal(Z.astype(np.float64), A.T @ Xm)
 
 
+# 16 column blocks (the most accumulators), as one column tile and as two
+@pytest.mark.parametrize("m,n,l", [(700, 500, 241), (257, 640, 250), (700, 500, 449),
+                                   (300, 777, 500), (500, 700, 512)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_pass_widest_tiles(R, m, n, l, dtype):
+    A = W.integer_matrix(m, n, seed=m + n)
+    Xn = W.integer_matrix(n, l, seed=l + 1)
+    Xm = W.integer_matrix(m, l, seed=l + 2)
+    Ad = dev(A, dtype)
+    Y = R.pass_(Ad, dev(Xn, dtype)).cpu().numpy()
+    Z = R.pass_(Ad, dev(Xm, dtype), trans=True).cpu().numpy()
+    assert np.array_equal(Y.astype(np.float64), A @ Xn)
+    assert np.array_equal(Z.astype(np.float64), A.T @ Xm)
+
+
 # ---- BF16 / FP8 passes ------------------------------------------------------
 # reductions shorter than a k-step and with a remainder, rows around a tile and
 # one more tile than compute units, l around the column blocks (288 / 289: one

@@ -230,3 +230,7 @@ def check(faults, rule, pick=lambda name: True):
 
 def test_operands_are_written_in_time(faults):
     check(faults, "operand")
+
+
+def test_results_are_there_in_time_fp32_fp64_passes(faults):
+    check(faults, "result", lambda name: "gemmreg" in name)
