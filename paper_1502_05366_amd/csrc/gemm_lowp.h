@@ -53,7 +53,6 @@ constexpr int NW = 4;
 constexpr int SB = 128;            // bytes of k per step
 constexpr int NS = 4;              // LDS stages of Xt
 constexpr int MAX_NB = 18;
-constexpr int SCALE_ONE = 127;     // E8M0 block scale 2^0
 
 struct Args {
   const uint8_t* A; int64_t lda;   // bytes
@@ -96,8 +95,11 @@ template <> struct Opnd<1> {
 // (Through the builtins the register allocator moved accumulators between
 // the two files inside the k loop, 150 - 250 moves per step, and spilled.)
 // The compiler does not see a matrix instruction here: a value written by an
-// ordinary vector instruction is used two instructions later at the earliest,
-// and the accumulators are read only after acc_settle().
+// ordinary vector instruction is used two wait states later at the earliest
+// (opnd_settle), and the accumulators are read or moved only after acc_settle (the
+// register allocator spills some between the k loop and its rest).  Both are tied
+// to the registers they stand for: a bare wait leaves the compiler free to move
+// other accesses of them across it.
 #if defined(__HIP_DEVICE_COMPILE__)
 template <int ELT, bool AC, int KK>
 __device__ __forceinline__ void mma(f4& acc, const Opnd<ELT>& a, const Opnd<ELT>& b) {
@@ -116,10 +118,28 @@ __device__ __forceinline__ void mma(f4& acc, const Opnd<ELT>& a, const Opnd<ELT>
   }
 }
 // vector writes of the operands have reached the matrix core (two wait states)
-__device__ __forceinline__ void opnd_settle() { asm volatile("s_nop 1" ::: "memory"); }
+template <int ELT> __device__ __forceinline__ void opnd_settle(Opnd<ELT> (&av)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (ELT == 2) asm volatile("" : "+v"(av[i].h[0]), "+v"(av[i].h[1]));
+    else asm volatile("" : "+v"(av[i].h));
+  }
+  asm volatile("s_nop 1" ::: "memory");
+}
+// the accumulators (block j < 16 in the accumulation registers)
+template <int NB> __device__ __forceinline__ void acc_tie(f4 (&acc)[4][NB]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (j < 16) asm volatile("" : "+a"(acc[i][j]));
+      else asm volatile("" : "+v"(acc[i][j]));
+    }
+}
 // the last products (at most 8 passes, 32 cycles) have written their results
-__device__ __forceinline__ void acc_settle() {
+template <int NB> __device__ __forceinline__ void acc_settle(f4 (&acc)[4][NB]) {
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+  acc_tie(acc);
 }
 // a copy the optimizer keeps: the loaded register is free for the next load
 __device__ __forceinline__ uint32_t move_u32(uint32_t x) {
@@ -131,8 +151,9 @@ __device__ __forceinline__ uint32_t move_u32(uint32_t x) {
 #else   // (the host pass does not know the register constraints)
 template <int ELT, bool AC, int KK>
 __device__ void mma(f4& acc, const Opnd<ELT>& a, const Opnd<ELT>& b);
-__device__ void opnd_settle();
-__device__ void acc_settle();
+template <int ELT> __device__ void opnd_settle(Opnd<ELT> (&av)[4]);
+template <int NB> __device__ void acc_tie(f4 (&acc)[4][NB]);
+template <int NB> __device__ void acc_settle(f4 (&acc)[4][NB]);
 __device__ uint32_t move_u32(uint32_t x);
 #endif
 
@@ -271,6 +292,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  acc_tie(acc);
 
   Opnd<ELT> bq[2][GB];                            // operand groups of Xt: current, next
   auto bread = [&](int slot, const uint8_t* st, int grp) {
@@ -355,7 +377,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
       for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) av[rb].set(kk, operand<ELT, TRANS>(r, rb, kk));
-      opnd_settle();
+      opnd_settle<ELT>(av);
       __builtin_amdgcn_sched_barrier(0);
       const int64_t ta = min(t + 2, last), tx = min(t + 3, last);
       const int bx = (int)((t - kb + 3) % NS);
@@ -369,6 +391,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
       kstep(r0, t, 0);
       kstep(r1, t + 1, NG & 1);
     }
+    acc_settle(acc);
   }
   if (sp == S - 1) {
     // the rest: both operands masked to zero past K
@@ -407,13 +430,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) av[rb].set(kk, operand<ELT, TRANS>(r, rb, kk));
       __syncthreads();
-      opnd_settle();
+      opnd_settle<ELT>(av);
       bread(0, sm, 0);
       step(av, sm, sm, 0, [](int) {});
+      acc_settle(acc);
     }
   }
 
-  acc_settle();
   // --- results -------------------------------------------------------------
   // row of element v of block rb: 16 rb + 4 q + v, or 4 (4 q + v) + rb transposed
   float* P = S > 1 ? g.part + ((p - g.W) * S + sp) * (int64_t)(BM * BN) : nullptr;

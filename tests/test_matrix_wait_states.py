@@ -234,3 +234,7 @@ def test_operands_are_written_in_time(faults):
 
 def test_results_are_there_in_time_fp32_fp64_passes(faults):
     check(faults, "result", lambda name: "gemmreg" in name)
+
+
+def test_results_are_there_in_time(faults):
+    check(faults, "result")
