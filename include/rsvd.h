@@ -40,14 +40,20 @@
  *   and its steps (orth works on column blocks of at most 256 above 256),
  *   l <= 256 when the ID or CUR is requested, for the derivative and the
  *   blocked QB, l <= 80 in a batch.  p >= 0, q >= 0, 1 <= k <= min(m, n).
- * - Co-residency: the pivoted QR (ID, CUR) and the block Jacobi (l > 64) run
- *   as ordinary launches of up to one workgroup per compute unit whose
- *   workgroups wait for each other with bounded spins.  They assume the
- *   call's kernels are not starved of compute units by concurrent kernels on
- *   other streams; if a wait gives up, the call reports RSVD_INFO_BARRIER and
- *   its outputs are invalid.  rsvd_decompose with both the SVD and the ID or
- *   CUR runs the Jacobi beside the pivoted QRs and keeps 8 compute units for
- *   it, so it needs the whole device.
+ * - Co-residency: the pivoted QR (ID, CUR) runs as an ordinary launch of up to
+ *   one workgroup per compute unit, the block Jacobi (64 < l <= 576) as one of
+ *   l / 32 rounded up (at most 18), one to a compute unit, whose workgroups wait
+ *   for each other with bounded spins.  They assume the call's kernels are not
+ *   starved of compute units by concurrent kernels on other streams; if a wait
+ *   gives up, the call reports RSVD_INFO_BARRIER and its outputs are invalid.
+ *   Where rsvd_svd, rsvd_svd_ex, rsvd_svd_noalloc, rsvd_svd_grad or
+ *   rsvd_small_svd calls it, the block Jacobi first tries 8 smaller workgroups
+ *   for each of these (at most 144, three to a compute unit): they start the
+ *   iteration only when all of them are resident, and otherwise leave it to the
+ *   launch above after a fraction of a millisecond, with the same results.
+ *   rsvd_decompose with both the SVD and the ID or CUR runs the Jacobi beside
+ *   the pivoted QRs and keeps 8 compute units for it, so it needs the whole
+ *   device.
  * - The Gaussian test matrix is drawn from Philox4x32-10 (key = seed) with
  *   Box-Muller normals: sketch entry (i, j) is normal number j*n + i of
  *   stream 0 (see rsvd_sketch).

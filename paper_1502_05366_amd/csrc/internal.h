@@ -131,17 +131,20 @@ hipError_t launch_zero_dep_rows(double* R, int64_t ldr, int l, int lp, const int
 // work: jacobi_work_bytes(l) bytes; sweeps_out (device int, may be null)
 // receives the number of sweeps of the block iteration.  The block iteration
 // (l > 64) waits across the workgroups of one ordinary launch (bounded spins,
-// INFO_BARRIER on give-up): without an exchange area at most 8 for l <= 256, and
-// the caller keeps that many CUs free of other waiting kernels; with one (xch,
+// INFO_BARRIER on give-up): at most 18, 8 for l <= 256, and the caller keeps that
+// many CUs free of other waiting kernels.  With an exchange area (xch,
 // jacobi_exchange_bytes(l) bytes, unused by others until the iteration ends) up to
-// 144 small ones.  giveup_test: every cross-workgroup wait waits for a
-// value no workgroup posts, with a small spin cap (failure-handling tests).
+// 144 small workgroups do it where all of them become resident at once, to the same
+// bits.  test (failure handling): JACOBI_TEST_GIVEUP, every wait in the iteration
+// waits for a value no workgroup posts, with a small spin cap; JACOBI_TEST_NO_ROOM,
+// the small workgroups wait for one more than there are.
+enum { JACOBI_TEST_GIVEUP = 1, JACOBI_TEST_NO_ROOM = 2 };
 size_t jacobi_work_bytes(int l);
 size_t jacobi_exchange_bytes(int l);
 hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* work, double* S,
                          double* Uh, int64_t lduh, double* Vh, int64_t ldvh, int max_sweeps,
-                         int32_t* info, int32_t* sweeps_out, bool giveup_test, hipStream_t s,
-                         double* xch, size_t xch_bytes, int ncu);
+                         int32_t* info, int32_t* sweeps_out, int test, hipStream_t s, double* xch,
+                         size_t xch_bytes, int ncu);
 
 // ------------------------------------------------------------------ cpqr --
 struct CpqrPlan {

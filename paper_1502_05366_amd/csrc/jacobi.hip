@@ -103,7 +103,12 @@ struct JacArgs {
   uint32_t spin_cap;
   int32_t* info;
   int32_t* sweeps_out;
+  const uint32_t* split_state;   // null, or the state of a split launch before this one
 };
+
+// Whether the workgroups of a split launch (below) run the iteration or leave it to
+// the launch after it.
+enum : uint32_t { SPLIT_UNDECIDED = 0, SPLIT_RUNS = 1, SPLIT_LEAVES = 2 };
 
 // spin until workgroup v has completed `target` rounds (bounded: past the cap
 // the wait gives up, raises the abort flag and INFO_BARRIER)
@@ -321,6 +326,7 @@ __device__ __forceinline__ void jac_steps(double* G, double* Jm, const int* ptab
 
 template <int JRPL, int NW>
 __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
+  if (a.split_state != nullptr && ld_agent_u32(a.split_state) == SPLIT_RUNS) return;   // (done)
   using D = JacDims<JRPL, NW>;
   constexpr int NT = D::NT, RTW = D::RTW;
   extern __shared__ double smem[];
@@ -517,8 +523,17 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
 //
 // 4 waves, 47 KB of LDS and at most 168 registers: three workgroups fit on a
 // compute unit, so that the 8 nbp / 2 <= 144 workgroups of one launch, which wait
-// for each other, need 48 of them.
+// for each other, need 48 of them.  Kernels of other streams may hold that many (a
+// pivoted QR takes every compute unit and waits within itself), and two launches
+// that each wait for compute units of the other would both give up.  So the
+// workgroups meet before they touch anything: the iteration starts when all of them
+// are resident, and when they are not within MEET_CAP polls (~0.3 ms; they start
+// within microseconds on an idle device) all leave and jacobi_block_kernel, launched
+// after this kernel in any case, does the iteration with one workgroup per pair, to
+// the same bits.  The meeting and the launch that has nothing to do do not show in the
+// time of a small SVD (l = 80: 864 us without them, 856 with; 220: 3.75 / 3.70 ms).
 constexpr int SPLIT = 8;
+constexpr uint32_t MEET_CAP = 256;
 
 struct JacSplit {
   JacArgs j;
@@ -526,7 +541,34 @@ struct JacSplit {
   uint32_t* gtags;      // [G][SPLIT] FLAG_STRIDE apart, a word per tile: rounds posted
   uint32_t* wtags;      // [G][SPLIT] rounds whose rows of W are written
   uint32_t* vtags;      // [G][SPLIT] the same for V
+  uint32_t* state;      // SPLIT_*; FLAG_STRIDE on: the number of workgroups that have started
+  uint32_t meet, meet_cap;   // workgroups to wait for, polls before leaving
 };
+
+// Every workgroup's first step: true when all `meet` workgroups are resident.  One
+// compare-and-swap decides for all of them, and a workgroup that starts after the
+// decision to leave finds it.
+__device__ __forceinline__ bool split_meet(const JacSplit& b) {
+  __shared__ uint32_t state;
+  if (threadIdx.x == 0) {
+    auto decide = [&](uint32_t v) {
+      uint32_t undecided = SPLIT_UNDECIDED;
+      __hip_atomic_compare_exchange_strong(b.state, &undecided, v, __ATOMIC_RELAXED,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const uint32_t n = __hip_atomic_fetch_add(b.state + FLAG_STRIDE, 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+    if (n + 1u == b.meet) decide(SPLIT_RUNS);
+    uint32_t st, polls = 0;
+    while ((st = ld_agent_u32(b.state)) == SPLIT_UNDECIDED) {
+      if (++polls >= b.meet_cap) decide(SPLIT_LEAVES);
+      __builtin_amdgcn_s_sleep(1);
+    }
+    state = st;
+  }
+  __syncthreads();
+  return state == SPLIT_RUNS;
+}
 
 template <int RTW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void
@@ -540,6 +582,7 @@ jacobi_split_kernel(JacSplit b) {
   __shared__ double Jm[JJ * GLD];           // J(c, j) at c GLD + j
   __shared__ int ptab[(BS - 1) * BS];       // inner steps: p | q << 8 of pair P in step t
   __shared__ int rotated, rround;
+  if (!split_meet(b)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lg = lane >> 4;
@@ -809,8 +852,9 @@ size_t jacobi_work_bytes(int l) {
          JCTL * FLAG_STRIDE * sizeof(uint32_t) + (size_t)l * sizeof(double) + 256;
 }
 
-// the exchange area of the split iteration: partial Grams, then three sets of tags
-static size_t split_words(int G) { return (size_t)3 * G * SPLIT * FLAG_STRIDE; }
+// the exchange area of the split iteration: partial Grams, then three sets of tags,
+// the state and the count of workgroups
+static size_t split_words(int G) { return (size_t)(3 * G * SPLIT + 2) * FLAG_STRIDE; }
 size_t jacobi_exchange_bytes(int l) {
   if (l <= LDS_MAX_L) return 0;
   const int G = jac_cols(l) / BS / 2;
@@ -830,8 +874,8 @@ hipError_t launch_block(JacArgs& a, hipStream_t s) {
 
 hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* work, double* S,
                          double* Uh, int64_t lduh, double* Vh, int64_t ldvh, int max_sweeps,
-                         int32_t* info, int32_t* sweeps_out, bool giveup_test, hipStream_t s,
-                         double* xch, size_t xch_bytes, int ncu) {
+                         int32_t* info, int32_t* sweeps_out, int test, hipStream_t s, double* xch,
+                         size_t xch_bytes, int ncu) {
   if (l > JACOBI_MAX_L) return hipErrorInvalidValue;
   const double tol = (double)l * 2.220446049250313e-16;
   if (l <= LDS_MAX_L) {
@@ -858,13 +902,14 @@ hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* wo
   a.tags = ctl;                                   // 64 flags
   a.rot = ctl + 64 * FLAG_STRIDE;                 // 2 x 64 flags
   a.abort_flag = ctl + 192 * FLAG_STRIDE;
-  a.wait_bias = giveup_test ? 1u : 0u;
-  a.spin_cap = giveup_test ? (1u << 10) : (1u << 22);
+  a.wait_bias = test == JACOBI_TEST_GIVEUP ? 1u : 0u;
+  a.spin_cap = test == JACOBI_TEST_GIVEUP ? (1u << 10) : (1u << 22);
   a.info = info;
   a.sweeps_out = sweeps_out;
+  a.split_state = nullptr;
   // Split where the caller lends the exchange area and 8 workgroups per pair find
-  // room at two to a compute unit (three fit); beside a pivoted QR, which takes
-  // all but a few compute units, a pair has one workgroup.
+  // room at two to a compute unit (three fit); beside a pivoted QR of the same call,
+  // which takes all but a few compute units, a pair has one workgroup.
   const bool split = xch && xch_bytes >= jacobi_exchange_bytes(l) && a.G * SPLIT <= 2 * ncu;
   JacSplit b;
   b.j = a;
@@ -872,6 +917,9 @@ hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* wo
   b.gtags = reinterpret_cast<uint32_t*>(xch + (size_t)2 * a.G * SPLIT * 768);
   b.wtags = b.gtags + a.G * SPLIT * FLAG_STRIDE;
   b.vtags = b.wtags + a.G * SPLIT * FLAG_STRIDE;
+  b.state = b.vtags + a.G * SPLIT * FLAG_STRIDE;
+  b.meet = (uint32_t)(a.G * SPLIT) + (test == JACOBI_TEST_NO_ROOM ? 1u : 0u);
+  b.meet_cap = MEET_CAP;
   const int nx = split ? (int)split_words(a.G) : 0;
   // one thread per element of W and per control word
   const int64_t ninit =
@@ -884,10 +932,10 @@ hipError_t launch_jacobi(const double* Rh, int64_t ldr, int l, int k, double* wo
     const dim3 grid((unsigned)(a.G * SPLIT));
     if (l <= 256) hipLaunchKernelGGL(jacobi_split_kernel<2>, grid, dim3(256), 0, s, b);
     else hipLaunchKernelGGL(jacobi_split_kernel<5>, grid, dim3(256), 0, s, b);
-    e = hipGetLastError();
-  } else {
-    e = (l <= 256) ? launch_block<16, 8>(a, s) : launch_block<40, 8>(a, s);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    a.split_state = b.state;
   }
+  e = (l <= 256) ? launch_block<16, 8>(a, s) : launch_block<40, 8>(a, s);
   if (e != hipSuccess) return e;
   double* sig = reinterpret_cast<double*>(ctl + JCTL * FLAG_STRIDE);
   const unsigned nwg = (unsigned)cdiv(l, JOW);

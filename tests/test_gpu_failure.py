@@ -9,6 +9,8 @@ with a small spin cap.  The status bits are those of the rank / failure
 reporting of Sec. 2.6 (frank) extended with the library's own conditions.
 """
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -119,3 +121,42 @@ def test_wait_giveup_reports_barrier(R, what):
     J, T, pv, info = R.cpqr(dev(Bc), r, k)
     assert info_word(info) == 0
     assert np.array_equal(np.sort(J.cpu().numpy()), np.arange(c))
+
+
+# The block Jacobi on 8 small workgroups per block pair starts only when all of them
+# are resident, which kernels on other streams can prevent; then one workgroup per
+# pair does it.  The library's internal launcher has a test mode in which the small
+# workgroups wait for one more than there are.
+LAUNCH_JACOBI = "_ZN4rsvd13launch_jacobiEPKdliiPdS2_S2_lS2_liPiS3_iP12ihipStream_tS2_mi"
+NO_ROOM = 2
+
+
+@pytest.mark.parametrize("l", [65, 120, 256, 257, 400, 576])
+def test_small_svd_without_room_for_split(R, l):
+    from paper_1502_05366_amd import _lib
+    lib = _lib.load()
+    launch = getattr(lib, LAUNCH_JACOBI)
+    i, i64, p = ctypes.c_int, ctypes.c_int64, ctypes.c_void_p
+    launch.restype = i
+    launch.argtypes = [p, i64, i, i, p, p, p, i64, p, i64, i, p, p, i, p, p, ctypes.c_size_t, i]
+    k = l // 2
+    g = np.random.default_rng(l)
+    Rh = dev(np.triu(g.standard_normal((l, l))) + 3 * np.eye(l))
+    S, Uh, Vh, info = R.small_svd(Rh, k)
+    assert info_word(info) == 0
+    nbytes = lib.rsvd_small_svd_workspace_bytes(l)
+    area = torch.empty(2 * nbytes, dtype=torch.uint8, device="cuda")
+    work = area.data_ptr()
+    xch = work + (nbytes + 255) // 256 * 256
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    S2, U2, V2 = torch.zeros_like(S), torch.zeros_like(Uh), torch.zeros_like(Vh)
+    info2 = torch.zeros(2, dtype=torch.int32, device="cuda")
+    print("block Jacobi without room for its split form, l =", l, flush=True)
+    for _ in range(2):                            # (the exchange area as the first call left it)
+        rc = launch(Rh.data_ptr(), l, l, k, work, S2.data_ptr(), U2.data_ptr(), k, V2.data_ptr(), k,
+                    40, info2.data_ptr(), None, NO_ROOM, torch.cuda.current_stream().cuda_stream,
+                    xch, area.data_ptr() + area.numel() - xch, ncu)
+        assert rc == 0
+        torch.cuda.synchronize()
+        assert info_word(info2) == 0
+        assert torch.equal(S, S2) and torch.equal(Uh, U2) and torch.equal(Vh, V2)
