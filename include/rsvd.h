@@ -280,6 +280,12 @@ int rsvd_svd_grad(rsvd_handle_t h, int dtype, int64_t m, int64_t n, int k, int p
  *   16-byte aligned); U_i (m_i x k_i FP32, ld k_i) at u_off[i]; S_i (k_i FP64,
  *   descending) at s_off[i]; V_i (n_i x k_i FP32, ld k_i) at v_off[i]; the
  *   totals in a_elems, u_elems, s_elems, v_elems.
+ * rsvd_batch_workspace_bytes: the matrices with l <= 64 run on two workgroups
+ *   per compute unit, those with a larger l on one, and each workgroup has a slot
+ *   of its own in the workspace: lp (4 m + 4 n + 8 max(m, n)) + 16 lp^2 bytes at
+ *   the largest m, n and lp = l rounded up to 16 of its kind (4096 matrices of up
+ *   to 2048 x 1024, l <= 72, on 256 compute units: 1.6 GB).  No more workgroups
+ *   than matrices of a kind.
  * rsvd_batch_prepare: copies the plan's descriptor table into the workspace
  *   (rsvd_batch_workspace_bytes bytes, 256-byte aligned) and synchronizes the
  *   stream; once per workspace, outside any stream capture.

@@ -28,7 +28,9 @@
 //    single-matrix small SVD, one column pair per 16 lanes);
 //  * U and V on FP64 MFMA, written in FP32.
 // Skinny matrices live in a per-workgroup slot of the workspace (L2-resident
-// for the sizes of a batch), small factors in LDS (l <= 80).
+// for the sizes of a batch), small factors in LDS (l <= 80).  A slot holds three,
+// each used in place for what follows it: Y and its basis Q; Omega, Z and its basis;
+// the FP64 first pass of an orth and, of the last one, its FP64 basis Qh.
 #include "common.h"
 #include "internal.h"
 #include "jacobi_dev.h"
@@ -646,9 +648,11 @@ __device__ __noinline__ void b_rinv(int l, int lp) {
 // Out (rows x ncols, ldo) = In (rows x lp, lp = 16 NB) a (lp x lp in LDS,
 // stride SL; columns >= ncols are formed but not written), on FP64 MFMA; a
 // 16-row block's operands are loaded before its products.
+// Out may be In (ldo = lp): a wave's block is read before it is written, by no other
+// wave.
 template <int NB, typename TI, typename TO>
-__device__ __noinline__ void b_apply(const TI* __restrict__ In, int64_t rows, int ncols,
-                                     TO* __restrict__ Out, int64_t ldo) {
+__device__ __noinline__ void b_apply(const TI* In, int64_t rows, int ncols, TO* Out,
+                                     int64_t ldo) {
   auto& g_lds = batch_lds<ml_of<NB>()>();
   constexpr int SL = BatchLds<ml_of<NB>()>::SL;
   (void)SL;
@@ -688,8 +692,6 @@ __device__ __noinline__ void b_apply(const TI* __restrict__ In, int64_t rows, in
   __syncthreads();
 }
 
-// Q (rows x lp) = orth(In) by CholeskyQR2 in FP64; T (rows x lp FP64) holds
-// the first pass.
 // ||G - I||_F^2 of the leading l x l block of the Gram in a (upper blocks:
 // diagonal terms once, off-diagonal ones twice), the same value on every
 // thread
@@ -775,6 +777,8 @@ __device__ __noinline__ void b_replace(double* T, int64_t rows, int l, int lp, u
   __syncthreads();
 }
 
+// Q (rows x lp) = orth(In) by CholeskyQR2 in FP64; T (rows x lp FP64) holds
+// the first pass.  Q may be In, or T where it is FP64.
 template <int NB, typename TI, typename TO>
 __device__ void b_orth(const TI* In, int64_t rows, int l, double* T, TO* Q, uint32_t k0,
                        uint32_t k1, uint32_t word) {
@@ -789,7 +793,7 @@ __device__ void b_orth(const TI* In, int64_t rows, int l, double* T, TO* Q, uint
   if (g_lds.ndep > 0) b_replace<ML>(T, rows, l, lp, k0, k1, word);
   b_gram<NB>(T, rows);
   if (b_gram_offset2<ML>(l) <= ORTH_SKIP2) {
-    b_copy(T, rows, lp, Q);
+    if ((const void*)T != (const void*)Q) b_copy(T, rows, lp, Q);
     return;
   }
   b_chol<ML>(l, lp);
@@ -863,12 +867,10 @@ __device__ void b_load_small(const double* M, int l, int k, int lp) {
   __syncthreads();
 }
 
-// The decomposition of one matrix after its sketch, for lp = 16 NB.
+// The decomposition of one matrix after its sketch (in Z), for lp = 16 NB.
 template <int NB, int RPW, int KC>
 __device__ __noinline__ void b_one(const BatchArgs& g, const BatchDesc& d, const float* A,
-                                   const float* Om,
-                      float* Y, float* Q, float* Z, float* Zq, double* T, double* Qh,
-                      double* Uh, double* Vh) {
+                                   float* Y, float* Z, double* T, double* Uh, double* Vh) {
   auto& g_lds = batch_lds<ml_of<NB>()>();
   constexpr int SL = BatchLds<ml_of<NB>()>::SL;
   (void)SL;
@@ -878,15 +880,17 @@ __device__ __noinline__ void b_one(const BatchArgs& g, const BatchDesc& d, const
   // batch word of the replacement columns: orth call (high bits), matrix
   const uint32_t mw = (uint32_t)d.index & 0xFFFFFu;
   uint32_t call = 0;
-  b_pass_n<NB, RPW, KC>(A, d.lda, m, n, Om, Y);
+  b_pass_n<NB, RPW, KC>(A, d.lda, m, n, Z, Y);
   for (int j = 0; j < g.q; ++j) {
-    b_orth<NB>(Y, m, l, T, Q, g.k0, g.k1, (call++ << 20) | mw);
-    b_pass_t<NB, RPW, KC>(A, d.lda, m, n, Q, Z);
-    b_orth<NB>(Z, n, l, T, Zq, g.k0, g.k1, (call++ << 20) | mw);
-    b_pass_n<NB, RPW, KC>(A, d.lda, m, n, Zq, Y);
+    b_orth<NB>(Y, m, l, T, Y, g.k0, g.k1, (call++ << 20) | mw);
+    b_pass_t<NB, RPW, KC>(A, d.lda, m, n, Y, Z);
+    b_orth<NB>(Z, n, l, T, Z, g.k0, g.k1, (call++ << 20) | mw);
+    b_pass_n<NB, RPW, KC>(A, d.lda, m, n, Z, Y);
   }
+  float* Q = Y;
   b_orth<NB>(Y, m, l, T, Q, g.k0, g.k1, (call++ << 20) | mw);
   b_pass_t<NB, RPW, KC>(A, d.lda, m, n, Q, Z);   // B^T
+  double* Qh = T;
   b_orth<NB>(Z, n, l, T, Qh, g.k0, g.k1, (call++ << 20) | mw);
   b_xty<ML>(Qh, Z, n, lp);                         // Rh = Qh^T B^T
   if (threadIdx.x == 0 && g_lds.flag) info_or(g.info, INFO_ORTH_FALLBACK);
@@ -902,13 +906,9 @@ template <int ML> __device__ __forceinline__ void batch_rsvd(const BatchArgs& g)
   auto& g_lds = batch_lds<ML>();
   const int tid = threadIdx.x;
   char* slot = g.scratch + (int64_t)blockIdx.x * g.slot_bytes;
-  float* Om = reinterpret_cast<float*>(slot + g.off_om);
   float* Y = reinterpret_cast<float*>(slot + g.off_y);
-  float* Q = reinterpret_cast<float*>(slot + g.off_q);
   float* Z = reinterpret_cast<float*>(slot + g.off_z);
-  float* Zq = reinterpret_cast<float*>(slot + g.off_zq);
   double* T = reinterpret_cast<double*>(slot + g.off_t);
-  double* Qh = reinterpret_cast<double*>(slot + g.off_qh);
   double* Uh = reinterpret_cast<double*>(slot + g.off_uh);
   double* Vh = reinterpret_cast<double*>(slot + g.off_vh);
   for (;;) {
@@ -925,13 +925,13 @@ template <int ML> __device__ __forceinline__ void batch_rsvd(const BatchArgs& g)
       g_lds.nonfinite = 0;
     }
     __syncthreads();
-    b_sketch<ML>(Om, d.n, d.l, lp, g.k0, g.k1, (uint32_t)d.index);
+    b_sketch<ML>(Z, d.n, d.l, lp, g.k0, g.k1, (uint32_t)d.index);
     // (lp / 16, pass shape) -> one instantiation
 #define RSVD_B1(NBV)                                                                     \
   switch (d.variant) {                                                                   \
-    case 1: b_one<NBV, 2, 32>(g, d, A, Om, Y, Q, Z, Zq, T, Qh, Uh, Vh); break;           \
-    case 2: b_one<NBV, 1, 32>(g, d, A, Om, Y, Q, Z, Zq, T, Qh, Uh, Vh); break;           \
-    default: b_one<NBV, 1, 64>(g, d, A, Om, Y, Q, Z, Zq, T, Qh, Uh, Vh); break;          \
+    case 1: b_one<NBV, 2, 32>(g, d, A, Y, Z, T, Uh, Vh); break;                          \
+    case 2: b_one<NBV, 1, 32>(g, d, A, Y, Z, T, Uh, Vh); break;                          \
+    default: b_one<NBV, 1, 64>(g, d, A, Y, Z, T, Uh, Vh); break;                         \
   }
     if constexpr (ML == BATCH_SMALL_LP) {
       switch (lp / 16) {

@@ -247,7 +247,7 @@ struct BatchArgs {
   float* V;
   char* scratch;                     // one slot of slot_bytes per workgroup
   int64_t slot_bytes;
-  int64_t off_om, off_y, off_q, off_z, off_zq, off_t, off_qh, off_uh, off_vh;
+  int64_t off_y, off_z, off_t, off_uh, off_vh;
   uint32_t k0, k1;                   // seed words
   int q;
   int32_t* info;

@@ -55,7 +55,7 @@ struct rsvd_batch_s {
     int64_t first, count;
     int grid;
     int64_t slot_off, slot_bytes;
-    int64_t off_om, off_y, off_q, off_z, off_zq, off_t, off_qh, off_uh, off_vh;
+    int64_t off_y, off_z, off_t, off_uh, off_vh;
   } part[2];
   int64_t desc_off;
   size_t work_bytes;
@@ -1398,13 +1398,9 @@ int rsvd_batch_create(rsvd_handle_t h, int64_t count, const int64_t* m, const in
     pt.grid = (int)std::min<int64_t>((t + 1) * (int64_t)h->ncu, pt.count);
     const int64_t rmax = std::max(mmax, nmax);
     int64_t o = 0;
-    pt.off_om = o; o = r256(o + nmax * lpm * 4);
     pt.off_y = o;  o = r256(o + mmax * lpm * 4);
-    pt.off_q = o;  o = r256(o + mmax * lpm * 4);
     pt.off_z = o;  o = r256(o + nmax * lpm * 4);
-    pt.off_zq = o; o = r256(o + nmax * lpm * 4);
     pt.off_t = o;  o = r256(o + rmax * lpm * 8);
-    pt.off_qh = o; o = r256(o + nmax * lpm * 8);
     pt.off_uh = o; o = r256(o + lpm * lpm * 8);
     pt.off_vh = o; o = r256(o + lpm * lpm * 8);
     pt.slot_bytes = o;
@@ -1516,8 +1512,7 @@ int rsvd_batch_svd(rsvd_batch_t b, uint64_t seed, const float* A, float* U, doub
     g.A = A; g.U = U; g.S = S; g.V = V;
     g.scratch = w + pt.slot_off;
     g.slot_bytes = pt.slot_bytes;
-    g.off_om = pt.off_om; g.off_y = pt.off_y; g.off_q = pt.off_q; g.off_z = pt.off_z;
-    g.off_zq = pt.off_zq; g.off_t = pt.off_t; g.off_qh = pt.off_qh; g.off_uh = pt.off_uh;
+    g.off_y = pt.off_y; g.off_z = pt.off_z; g.off_t = pt.off_t; g.off_uh = pt.off_uh;
     g.off_vh = pt.off_vh;
     g.k0 = (uint32_t)seed; g.k1 = (uint32_t)(seed >> 32);
     g.q = b->q;

@@ -277,3 +277,29 @@ def test_batch_rejects_unprepared_workspace(R):
     assert rc == -7
     plan.run(buf, 1)                                      # the prepared one works
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("ms,ns,ks,most", [
+    ("c4", None, None, 1.5), ([2048] * 600, [1024] * 600, [56] * 600, 1.0),
+    ([300] * 400, [900] * 400, [72] * 400, 1.0), ([4000] * 800, [64] * 800, [10, 60] * 400, 2.0)])
+def test_batch_workspace_size(R, ms, ns, ks, most):
+    """A slot per workgroup, and not far above one slot of nine separate matrices at lp =
+    80 per compute unit (which a launch of one workgroup per unit takes)."""
+    if ms == "c4":
+        ms, ns, ks = W.c4_dims()
+    ms, ns, ks = np.array(ms), np.array(ns), np.array(ks)
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    lp = (np.minimum(ks + 8, np.minimum(ms, ns)) + 15) // 16 * 16
+    up = lambda x: (int(x) + 255) // 256 * 256  # noqa: E731
+    want = 256 + up(64 * len(ms))
+    for sel, per in ((lp > 64, 1), (lp <= 64, 2)):
+        if sel.any():
+            m, n, p = ms[sel].max(), ns[sel].max(), lp[sel].max()
+            want += min(per * ncu, int(sel.sum())) * (
+                up(4 * m * p) + up(4 * n * p) + up(8 * max(m, n) * p) + 2 * up(8 * p * p))
+    m, n = ms.max(), ns.max()
+    one = min(ncu, len(ms)) * 80 * (12 * n + 8 * m + 8 * max(m, n) + 8 * n + 16 * 80)
+    got = R.BatchPlan(ms, ns, ks, 8, 1).work_bytes
+    print("batch workspace", got, "by the formula", want, "of one", got / one, flush=True)
+    assert abs(got - want) <= 512 + 64 * len(ms)           # (the descriptor table)
+    assert got <= most * one
