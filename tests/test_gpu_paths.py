@@ -113,6 +113,29 @@ def test_narrow_pass_edges(R, m, n, l, kind):
     assert np.array_equal(Z.cpu().numpy().astype(np.float64), A.T @ Xm)
 
 
+# results scaled and added to C over every column block: X of two FP8 terms (the
+# second of them exact here: its product is zero) and scales of powers of two
+@pytest.mark.parametrize("m,n,l", [(300, 260, 31), (257, 400, 250), (130, 1000, 288)])
+def test_f8_pass_adds_scaled_results(R, m, n, l):
+    g = np.random.default_rng(m + l)
+    A = W.integer_matrix(m, n, seed=m + n)
+    ld = (n + 15) // 16 * 16
+    Ad = padded(torch.as_tensor(A).to(torch.float8_e4m3fn).view(torch.uint8).numpy(),
+                torch.uint8, ld)
+    s = 2.0 ** g.integers(-3, 4, n)
+    # (a largest entry of 7 times a power of two in every column of diag(s) X and X)
+    Xn = np.clip(W.integer_matrix(n, l, seed=l + 1), -7, 7)
+    Xm = np.clip(W.integer_matrix(m, l, seed=l + 2), -7, 7)
+    Xn[0, :] = 7.0
+    Xm[0, :] = 7.0
+    t = 2.0 ** g.integers(-2, 3, l)
+    sd = dev(s, torch.float32)
+    Y = R.pass_f8(Ad, sd, dev(Xn * t / s[:, None], torch.float32), split=True)
+    Z = R.pass_f8(Ad, sd, dev(Xm * t, torch.float32), trans=True, split=True)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), A @ (Xn * t))
+    assert np.array_equal(Z.cpu().numpy().astype(np.float64), s[:, None] * (A.T @ (Xm * t)))
+
+
 # ---- orth: dependent columns and the second pass's test ----------------------
 # one and several column blocks (l around 16 and 64), the last block ragged;
 # every third column repeats the one before it
