@@ -59,8 +59,8 @@ struct Args {
   float* C; int64_t ldc;
   int64_t M, K, L;                 // elements
   int64_t nrt, nct;
-  int64_t P, W;                    // tile numbers; the first W are whole tiles,
-  int S;                           // the others in S k splits (partial tiles in part)
+  int64_t P, W;                    // tile numbers; the first W are whole tiles, the
+  int S;                           // others (W = 0: all tiles) in S k splits (in part)
   float* part;
   const float* xs;                 // FP8: L column scales (null: none)
   const float* rs;                 // FP8: M row scales (null: none)
@@ -227,14 +227,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
   // (the second read of A hits that XCD's L2) and the same k range of different
   // row tiles (the same lines of Xt).  The first g.W tiles are whole, the others
   // in S splits.  Numbers past the last row tile (of 8) have no tile.
+  // With W = 0 the pairs (row tile, split) take the place of the row tiles, so that a
+  // few row tiles in many splits reach all XCDs.
   const int64_t w = blockIdx.x;
   const int64_t rest = g.P - g.W;
-  const bool whole = w < g.W;
-  const int64_t p = whole ? w : g.W + (w - g.W) % rest;
+  const bool whole = w < g.W, pairs = g.W == 0;
+  const int64_t p = whole || pairs ? w : g.W + (w - g.W) % rest;
   const int S = whole ? 1 : g.S;
-  const int sp = whole ? 0 : (int)((w - g.W) / rest);
   const int64_t ct = (p / 8) % g.nct;
-  const int64_t rt = p % 8 + 8 * (p / 8 / g.nct);
+  const int64_t gt = p % 8 + 8 * (p / 8 / g.nct);
+  const int64_t rt = pairs ? gt % g.nrt : gt;
+  const int sp = whole ? 0 : (int)(pairs ? gt / g.nrt : (w - g.W) / rest);
+  if (sp >= S) return;
   if (rt >= g.nrt) return;                        // (the whole workgroup)
   const int64_t row0 = rt * BM;
   const int64_t col0 = ct * BN;
@@ -442,7 +446,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1))) void pa
   // store: a load between stores is waited for before the next one (FP8 pass
   // kernel, 1000 x 1000, l = 250: 59 -> 36 us; three passes at 65536 x 32768, l = 576,
   // one of them C +=: 4.29 -> 4.15 ms).
-  float* P = S > 1 ? g.part + ((p - g.W) * S + sp) * (int64_t)(BM * BN) : nullptr;
+  float* P = nullptr;
+  if (S > 1) P = g.part + ((pairs ? rt * g.nct + ct : p - g.W) * S + sp) * (int64_t)(BM * BN);
   auto rowloc = [&](int rb, int v) {
     return wave * 64 + (TRANS ? 4 * (4 * q + v) + rb : 16 * rb + 4 * q + v);
   };
@@ -497,8 +502,9 @@ template <int ELT, int NB>
 __global__ __launch_bounds__(256) void split_sum_kernel(Args g) {
   constexpr int BN = 16 * NB;
   const int64_t tile = blockIdx.x, p0 = g.W + tile;
-  const int64_t row0 = (p0 % 8 + 8 * (p0 / 8 / g.nct)) * BM;
-  const int64_t col0 = (p0 / 8 % g.nct) * BN;
+  const bool pairs = g.W == 0;
+  const int64_t row0 = (pairs ? tile / g.nct : p0 % 8 + 8 * (p0 / 8 / g.nct)) * BM;
+  const int64_t col0 = (pairs ? tile % g.nct : p0 / 8 % g.nct) * BN;
   const int e = (blockIdx.y * 256 + threadIdx.x) * 4;
   if (e >= BM * BN) return;
   const int64_t r = row0 + e / BN;
@@ -534,12 +540,13 @@ hipError_t run(const Args& g, hipStream_t s) {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
   if (e != hipSuccess) return e;
   const int64_t rest = g.P - g.W;
-  hipLaunchKernelGGL((pass_kernel<ELT, TRANS, NB>), dim3((unsigned)(g.W + rest * g.S)), dim3(NT),
-                     shm, s, g);
+  const int64_t grid = g.W ? g.W + rest * g.S : 8 * g.nct * cdiv(g.nrt * g.S, 8);
+  hipLaunchKernelGGL((pass_kernel<ELT, TRANS, NB>), dim3((unsigned)grid), dim3(NT), shm, s, g);
   e = hipGetLastError();
   if (e != hipSuccess || g.S == 1) return e;
   hipLaunchKernelGGL((split_sum_kernel<ELT, NB>),
-                     dim3((unsigned)rest, (unsigned)cdiv(BM * 16 * NB, 1024)), dim3(256), 0, s, g);
+                     dim3((unsigned)(g.W ? rest : g.nrt * g.nct),
+                          (unsigned)cdiv(BM * 16 * NB, 1024)), dim3(256), 0, s, g);
   return hipGetLastError();
 }
 
@@ -574,10 +581,44 @@ inline Plan plan(int elt, int64_t M, int64_t K, int64_t L, int ncu) {
     }
   }
   if (p.S == 1) p.W = p.P;
+  // Where that leaves more than half of the compute units idle (few row tiles and a
+  // short reduction: 1000 x 1000, l = 250, ran on 4 workgroups), also narrower column
+  // tiles and splits of as few as two steps: more workgroups, each with fewer steps
+  // and less code, which a small product waits for.  Chosen by a sum of microseconds
+  // as measured: a k-step 1.1 (the latency of its loads) or its products, a
+  // workgroup's start and end 4 + 1.1 per column block (code that runs once), the sum
+  // of the splits 5 and its partial tiles at 2 TB/s.  Pass and sum at l = 250, BF16 /
+  // FP8: 1000 x 1000 43 -> 16 / 59 -> 14 us, 4096 x 512 27 -> 16 / 51 -> 14; A^T X of
+  // 512 columns and 4096 rows the same way round, 25 + 5 -> 10 + 8 / 19 + 4 -> 8 + 6;
+  // 300 x 20000, l = 220: 44 + 13 -> 17 + 11 / 26 + 7 -> 20 + 8.
+  if (p.nrt * p.nct * p.S * 2 <= ncu) {
+    const int64_t ncb = cdiv(L, 16);
+    const int nb_max = p.nb;
+    double least = 1e30;
+    for (int nb = nb_max; nb >= 2; nb -= 2) {
+      const int64_t nct = cdiv(ncb, nb), tiles = p.nrt * nct, P = 8 * nct * cdiv(p.nrt, 8);
+      if (tiles > ncu) break;
+      for (int64_t S = 1; S == 1 || (S <= steps / 2 && tiles * S <= ncu); ++S) {
+        if (S > 1 && tiles * S * nb > (int64_t)2 * ncu * 16) break;
+        const double step = 0.055 * nb > 1.1 ? 0.055 * nb : 1.1;
+        const double t = (double)(cdiv(steps, S) + 1) * step + 4.0 + 1.1 * nb +
+                         (S > 1 ? 5.0 + (double)(S * p.nrt * nct * BM * 16 * nb) * 4.0 / 2e6 : 0.0);
+        if (t < least) {
+          least = t;
+          p.nb = nb;
+          p.nct = nct;
+          p.P = P;
+          p.S = (int)S;
+          p.W = S > 1 ? 0 : P;
+        }
+      }
+    }
+  }
   return p;
 }
 inline size_t part_bytes(const Plan& p) {
-  return p.S > 1 ? (size_t)((p.P - p.W) * p.S) * (size_t)(BM * 16 * p.nb) * sizeof(float) : 0;
+  const int64_t tiles = p.W ? p.P - p.W : p.nrt * p.nct;
+  return p.S > 1 ? (size_t)(tiles * p.S) * (size_t)(BM * 16 * p.nb) * sizeof(float) : 0;
 }
 
 // Fills in the tiling and launches (whole tiles when `part_cap` bytes do not

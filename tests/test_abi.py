@@ -200,3 +200,13 @@ def test_batch_create_argument_codes(lib):
     assert lib.rsvd_batch_svd(NULLP, 1, PTR, PTR, PTR, PTR, PTR, 1, PTR, NULLP) == -1
     assert lib.rsvd_batch_prepare(NULLP, PTR, 1, NULLP) == -1
     assert lib.rsvd_batch_set_variants(NULLP, PTR) == -1
+
+
+def test_small_narrow_passes_are_split(lib):
+    """BF16 products (M x K) X of few row tiles and a short reduction get two partial tiles
+    or more in the workspace (without, they ran on a handful of compute units)."""
+    for M, K, l in [(1000, 1000, 250), (1000, 1000, 32), (300, 2000, 100), (256, 1024, 512)]:
+        xt = (l + 15) // 16 * 16 * ((K + 31) // 32 * 32) * 2
+        for trans, m, n in ((0, M, K), (1, K, M)):
+            got = lib.rsvd_pass_workspace_bytes(2, trans, m, n, l)
+            assert got >= xt + 2 * M * l * 4, (M, K, l, trans, got)

@@ -113,6 +113,34 @@ def test_narrow_pass_edges(R, m, n, l, kind):
     assert np.array_equal(Z.cpu().numpy().astype(np.float64), A.T @ Xm)
 
 
+# few row tiles: column tiles of two blocks and up, splits of two steps and up, pairs
+# of row tile and split that do not fill the eight XCDs
+@pytest.mark.parametrize("m,n,l", [(1000, 1000, 250), (1024, 1024, 32), (300, 5000, 100),
+                                   (5000, 300, 220), (513, 2049, 576), (256, 700, 300),
+                                   (2600, 450, 130)])
+@pytest.mark.parametrize("kind", ["bf16", "f8"])
+def test_narrow_pass_few_tiles(R, m, n, l, kind):
+    A = W.integer_matrix(m, n, seed=m + n)
+    Xn = np.clip(W.integer_matrix(n, l, seed=l + 1), -7, 7)
+    Xm = np.clip(W.integer_matrix(m, l, seed=l + 2), -7, 7)
+    Xn[0, :] = 7.0
+    Xm[0, :] = 7.0
+    ld = (n + 15) // 16 * 16
+    if kind == "bf16":
+        Ad = padded(A, torch.bfloat16, ld)
+        Y = R.pass_(Ad, dev(Xn, torch.float32))
+        Z = R.pass_(Ad, dev(Xm, torch.float32), trans=True)
+    else:
+        Ad = padded(torch.as_tensor(A).to(torch.float8_e4m3fn).view(torch.uint8).numpy(),
+                    torch.uint8, ld)
+        sc = torch.ones(n, dtype=torch.float32, device="cuda")
+        Y = R.pass_f8(Ad, sc, dev(Xn, torch.float32))
+        Z = R.pass_f8(Ad, sc, dev(Xm, torch.float32), trans=True)
+    # (exact: integers, every partial sum below 2^24)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), A @ Xn)
+    assert np.array_equal(Z.cpu().numpy().astype(np.float64), A.T @ Xm)
+
+
 # results scaled and added to C over every column block: X of two FP8 terms (the
 # second of them exact here: its product is zero) and scales of powers of two
 @pytest.mark.parametrize("m,n,l", [(300, 260, 31), (257, 400, 250), (130, 1000, 288)])
