@@ -1,5 +1,6 @@
-// Batched randomized SVD of many small FP32 matrices in persistent launches: Alg. 5 (RSVD version II) with re-orthonormalization after every
-// product (Sec. 3.2, s = 1), applied to each matrix of the batch on its own.
+// Batched randomized SVD of many small FP32 matrices in persistent launches:
+// Alg. 5 (RSVD version II) with re-orthonormalization after every product (Sec.
+// 3.2, s = 1), applied to each matrix of the batch on its own.
 // The matrices are independent, as the blocks of Alg. 8 are, so each one is
 // the work of a single workgroup:
 //

@@ -9,8 +9,8 @@
 // The skinny operand X' (diag(s) X, or X) is quantized per output column:
 // t_j = max_k |X'_kj| / 448, X8 = e4m3(X' / t) (nearest, ties to even), and
 // the product is (op(A8) X8) diag(t) (diag(s) in the transposed case), with
-// v_mfma_scale_f32_16x16x128_f8f6f4 on E4M3 x E4M3 (unit block scales) and
-// FP32 accumulation.  A two-term split X' ~ t X8 + t2 X8lo (X8lo the codes of
+// v_mfma_f32_16x16x128_f8f6f4 on E4M3 x E4M3 (no block scales) and FP32
+// accumulation.  A two-term split X' ~ t X8 + t2 X8lo (X8lo the codes of
 // the residual with their own column scales t2) keeps about twice the
 // significand bits in the last projection, as the BF16 passes do.
 //

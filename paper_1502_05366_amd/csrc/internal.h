@@ -39,8 +39,7 @@ hipError_t launch_gemm(GemmTypes ty, bool trans, const void* A, int64_t lda, con
 // BF16 passes: C (FP32) = op(A) X, or C += op(A) X with accumulate, with A in
 // BF16 (lda % 8 == 0, 16-byte aligned) and Xt = X^T in BF16 (rup(L, 16) rows, L
 // of them used, ldx % 8 == 0, zero from K to ldx).  part: gemm_bf16_part_bytes
-// bytes for any number of compute units up to the one asked for (with less,
-// the reduction is not split).
+// bytes for the same ncu (with less, the reduction is not split).
 size_t gemm_bf16_part_bytes(int64_t M, int64_t K, int64_t L, int ncu);
 hipError_t launch_gemm_bf16(bool trans, const uint16_t* A, int64_t lda, const uint16_t* Xt,
                             int64_t ldx, float* C, int64_t ldc, int64_t M, int64_t K, int64_t L,

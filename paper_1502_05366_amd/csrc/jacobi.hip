@@ -510,7 +510,7 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
 // A round of jacobi_block_kernel is bound by its one workgroup per block pair:
 // at l = 576 it moves 0.65 MB and does 3.6 MFLOP of FP64 products on one compute
 // unit (12 us at the rate of its matrix cores) beside 16 serial rotation steps
-// (~5 us), 27 us in all, with 18 of 256 compute units at work.  Here workgroup
+// (~10 us), 29 us in all, with 18 of 256 compute units at work.  Here workgroup
 // (w, p) owns the rows of the 16-row tiles RTW p .. RTW p + RTW - 1 of pair w:
 // exactly one wave's share of the Gram sums above, so that adding the 8 partial
 // Grams in the order of p gives the same bits.  The parts exchange their partial
@@ -518,8 +518,8 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
 // the same rotation steps on the same G, and applies J to its own rows; part p of
 // the next owner waits for part p only.  The rows of V are not needed before the
 // end of a round: they are loaded while the steps run and written after W is
-// handed over.  29 -> 18 us a round at l = 576 (the rotation steps are 10 of them),
-// 19 -> 16 at l = 220.
+// handed over.  29 -> 18 us a round at l = 576 (10 of them the rotation steps as
+// before), 19 -> 16 at l = 220.
 //
 // 4 waves, 47 KB of LDS and at most 168 registers: three workgroups fit on a
 // compute unit, so that the 8 nbp / 2 <= 144 workgroups of one launch, which wait
@@ -530,8 +530,9 @@ __global__ __launch_bounds__(64 * NW) void jacobi_block_kernel(JacArgs a) {
 // are resident, and when they are not within MEET_CAP polls (~0.3 ms; they start
 // within microseconds on an idle device) all leave and jacobi_block_kernel, launched
 // after this kernel in any case, does the iteration with one workgroup per pair, to
-// the same bits.  The meeting and the launch that has nothing to do do not show in the
-// time of a small SVD (l = 80: 864 us without them, 856 with; 220: 3.75 / 3.70 ms).
+// the same bits.  The launch that has nothing to do takes 4.6 us; with the meeting it
+// does not show in the time of a small SVD (l = 80: 864 us without them, 856 with;
+// 220: 3.75 / 3.70 ms).
 constexpr int SPLIT = 8;
 constexpr uint32_t MEET_CAP = 256;
 

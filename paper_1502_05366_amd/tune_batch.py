@@ -1,5 +1,10 @@
 """Measure the batch pass-shape table (batch_tune, batch_tuning.json) on the
-current GPU: python -m paper_1502_05366_amd.tune_batch [--out PATH]."""
+current GPU: python -m paper_1502_05366_amd.tune_batch [--out PATH].
+
+Each bucket is timed alone.  In a mixed batch two matrices of different buckets share a
+compute unit, so the fastest shape alone need not be the fastest there: the committed
+table was measured with one workgroup per compute unit, and one measured with two (15
+buckets to shape 2) made 4096 mixed matrices slower, 26.95 -> 27.25 ms."""
 
 import argparse
 import json
