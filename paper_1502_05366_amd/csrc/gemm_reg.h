@@ -422,8 +422,7 @@ __global__ __launch_bounds__(NT)
         if (NG & 1) {
 #pragma unroll
           for (int p = 0; p < 4; ++p) bq[0][p] = bq[1][p];
-          settle_operands(bq[0]);
-        }
+        }                                         // (the barrier's wait follows)
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
       }
